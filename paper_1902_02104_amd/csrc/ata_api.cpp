@@ -398,6 +398,7 @@ int get_plan(int64_t m, int64_t n, int64_t cutoff, int variant, int max_depth, i
     if (flags & kPlanF64) po.split_tail = 1;
     else if (!(flags & kPlanReducedPrecision)) po.split_tail = 2;
     else if (flags & kPlanBf16Pair) po.split_tail = 3;
+    if (!(flags & (kPlanReducedPrecision | kPlanNoFine))) po.fine = (flags & kPlanF64) ? 1 : 2;
     if (flags & ATA_OPT_ADAPTIVE) {
         // Fractions of the MFMA peak measured on MI355X for this library's
         // tiles (rocprof MFMA busy of whole launches at 10000^2): FP64
@@ -542,8 +543,15 @@ hipError_t enqueue_product(const PlanDev& pdr, const char* dblob, const WsLayout
             err = launch_prep_lp(lp_mode, (const float*)A, lda, (int)m, (int)n, (int)L.ldt, scale, ws + L.t0,
                                  lp_mode == 0 ? (void*)(ws + L.t1) : nullptr, s);
     }
+    if (err == hipSuccess && P.fine_tb) {
+        // the whole product on fine tiles
+        ProfScope ps(ATA_KERNEL_SYRK, s);
+        err = launch_fine(f32, out64, P.fine_tb, (const char*)A + (int64_t)P.fine_row * lda * (f32 ? 4 : 8), lda,
+                          P.fine_k, (int)n, P.fine_parts, P.fine_rows, C_lower, P.fine_beta,
+                          P.fine_parts > 1 ? W + P.fine_off : nullptr, s);
+    }
     for (const PhaseDev& ph : pd->phases) {
-        if (err != hipSuccess) break;
+        if (err != hipSuccess || P.fine_tb) break;
         if (lp) {
             const float* scale = (const float*)(ws + L.scale);
             const void* t1 = lp_mode == 0 ? (const void*)(ws + L.t1) : nullptr;

@@ -118,6 +118,9 @@ constexpr int kPlanAccumulate = 0x80000;
 constexpr int kPlanF64 = 0x100000;
 // Internal plan flag: bfloat16-pair tiles (one resident workgroup per CU).
 constexpr int kPlanBf16Pair = 0x200000;
+// Internal plan flag: no fine tiles (the serving loop's grouped launches run
+// the SYRK items of a plan).
+constexpr int kPlanNoFine = 0x400000;
 // Equilibration in effect for a call with these option flags and this plan.
 bool want_equilibrate(int flags, const Plan& P, int dtype);
 int plan_flags(int flags, int dtype);

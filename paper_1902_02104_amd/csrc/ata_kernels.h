@@ -23,6 +23,13 @@ hipError_t launch_gemm(bool f32, bool out_f64, const void* A, int64_t lda, const
                        const WorkItem* items, int nitems, void* C, double* W, hipStream_t s,
                        const void* Aops = nullptr);
 
+// lower(A^t A) of K rows and n columns (packed C, beta 1 accumulates) on
+// tb x tb tiles (64 or 32), the rows in `parts` parts of `rows` rows; more
+// than one part writes FP64 partial tiles to `part` (tiles x parts x tb^2
+// doubles) and sums them in a second launch.
+hipError_t launch_fine(bool f32, bool out_f64, int tb, const void* A, int64_t lda, int K, int n, int parts, int rows,
+                       void* C, int beta, double* part, hipStream_t s);
+
 // FP64 tiles on 16-byte direct-to-LDS copies: nt = 1 for classical tiles
 // (TK_SYRK / TK_GEMM, and products on operand-sum buffers through Aops),
 // nt = 2 for Strassen product tiles with at most two terms per operand (and

@@ -574,6 +574,19 @@ std::vector<WorkItem>* tail_list(const PlanOptions& o, Phase& ph, bool mix_built
     return nullptr;
 }
 
+// Part count of `items` classical tiles alone (items of equal cost per unit
+// of K) of at most `want` parts: every part writes a partial tile and the sum
+// reads it back, so take the fewest parts whose rounds of the resident
+// workgroups come within half a percent of the best tile time.
+int64_t classical_parts(int64_t items, int64_t want) {
+    auto rounds = [&](int64_t p) { return (double)((items * p + kTileSlots - 1) / kTileSlots) / (double)p; };
+    double best = rounds(want);
+    for (int64_t p = 2; p < want; ++p) best = std::min(best, rounds(p));
+    for (int64_t p = 2; p <= want; ++p)
+        if (rounds(p) <= best * 1.005) return p;
+    return want;
+}
+
 // Split long K ranges of launches that have too few tiles to fill the GPU.
 // A task writing C becomes nparts tasks writing dense partial blocks to the
 // workspace plus a combination that sums them (in part order) into C; the
@@ -593,22 +606,8 @@ void split_k(Plan& P) {
         if (items > tail_slots(o.split_tail) && tail_list(o, ph, false)) continue;
         int64_t want = std::min<int64_t>(64, o.split_target / items);
         if (want < 2) continue;
-        if ((o.split_tail == 1 || o.split_tail == 2) && ph.str_items.empty() && ph.tg_items.empty()) {
-            // classical tiles alone (items of equal cost per unit of K): every
-            // part writes a partial tile and the sum reads it back, so take
-            // the fewest parts whose rounds of the resident workgroups come
-            // within half a percent of the best tile time up to `want` parts
-            auto rounds = [&](int64_t p) {
-                return (double)((items * p + kTileSlots - 1) / kTileSlots) / (double)p;
-            };
-            double best = rounds(want);
-            for (int64_t p = 2; p < want; ++p) best = std::min(best, rounds(p));
-            for (int64_t p = 2; p <= want; ++p)
-                if (rounds(p) <= best * 1.005) {
-                    want = p;
-                    break;
-                }
-        }
+        if ((o.split_tail == 1 || o.split_tail == 2) && ph.str_items.empty() && ph.tg_items.empty())
+            want = classical_parts(items, want);
         // decide a part count per task (workspace blocks: per combine block)
         std::map<int32_t, int> parts;  // task id -> parts
         auto decide = [&](int32_t id) {
@@ -860,6 +859,96 @@ void split_tail_rounds(Plan& P) {
     }
 }
 
+// Fine tiles (k_fine) for a plan that is one classical diagonal block of at
+// most one round of 128 x 128 tiles (kTileSlots of them; larger products
+// leave only a short last round, which split_tail_rounds balances).  Tile
+// size and part count are the ones with the least estimated time, and the
+// 128 x 128 tiles stay where theirs is within 5% of it.  The estimate, in
+// nanoseconds, from timings on gfx950 (m x n from 256 x 192 to 262144 x 300,
+// every part count up to 256):
+//  * a CU works off one row of a 64 x 64 tile in 32.5 (FP64) or 16 (FP32), of
+//    a 32 x 32 tile in 8.7 or 4.5, and in 1.15 times that alone on its CU;
+//    of a 128 x 128 tile in 140 or 82 alone and 236 or 148 for each of two;
+//  * workgroups beyond one round of kTileSlots share CUs unevenly: the mean
+//    of whole rounds and of a perfect balance;
+//  * a wave's stage (4 KB per operand) takes at least 900 (its latency), and
+//    a round of workgroups 2000 for the sum over waves and the stores;
+//  * staged operands leave the L2s at 9.5 bytes per picosecond; with a part
+//    count that is no multiple of eight the tiles of a part are spread over
+//    the XCDs, whose L2s then each fetch the rows (6.3 bytes per picosecond
+//    for up to eight copies of A: at 262144 x 300 FP64 32 x 32 tiles take
+//    578 us in 32 parts and 996 us in 34);
+//  * parts cost a second launch (5000) and their partial tiles written and
+//    read back (3 bytes per picosecond for both); up to 1024 rows stay in one
+//    part, at most 16 stages for each wave.
+bool fine_plan(Plan& P) {
+    const PlanOptions& o = P.opt;
+    if (!o.fine || P.phases.size() != 1 || P.tasks.size() != 1) return false;
+    const Phase& ph = P.phases[0];
+    const DevTask& t = P.tasks[0];
+    if (t.kind != TK_SYRK || t.nseg != 1 || t.dst != 0 || t.dM != P.n || !ph.combines.empty()) return false;
+    const int64_t items = (int64_t)ph.syrk_items.size();
+    if (items > kTileSlots) return false;
+    const int32_t* sg = P.segs.data() + t.seg_off;
+    const int64_t k = sg[2] - sg[1], n = P.n, es = o.fine == 1 ? 8 : 4;
+    const bool f64 = o.fine == 1, split = o.split_target > 0;
+    const int64_t kCUs = kTileSlots / 2;
+
+    // the 128 x 128 tiles, with the parts split_k gives them
+    int64_t p128 = 1;
+    const int64_t want = split ? std::min<int64_t>(64, o.split_target / items) : 1;
+    if (want >= 2) p128 = std::max<int64_t>(1, std::min(classical_parts(items, want), k / o.split_min_k));
+    const int64_t w128 = items * p128;
+    double best = (double)((k + p128 - 1) / p128) *
+                  (w128 > kCUs ? (double)((w128 + kTileSlots - 1) / kTileSlots) * (f64 ? 236 : 148) : (f64 ? 140 : 82));
+    if (p128 > 1) best += 5000 + (double)w128 * kGemmTile * kGemmTile * 16 / 3e3;
+    int tb = 0;
+    int64_t rows = k, parts = 1;
+    for (int b : {64, 32}) {
+        const int64_t tl = (n + b - 1) / b, tiles = tl * (tl + 1) / 2;
+        const int64_t ks = 4096 / (b * es);
+        const double row = b == 64 ? (f64 ? 32.5 : 16) : (f64 ? 8.7 : 4.5);
+        const double staged = (double)(2 * tiles - tl) * k * b * es, all = 8.0 * k * n * es;
+        int64_t last = -1;
+        for (int64_t p = 1; p <= (split && k > 1024 ? 512 : 1); ++p) {
+            const int64_t r = ((k + p - 1) / p + ks - 1) / ks * ks;
+            const int64_t np = (k + r - 1) / r, w = tiles * np;
+            if (np == last) continue;  // the same parts as the previous count
+            last = np;
+            if (p > 1 && (w > 4 * kTileSlots || r < 8 * ks)) break;
+            const double stages = (double)((r / ks + 3) / 4) * (double)((w + kTileSlots - 1) / kTileSlots);
+            const double cu = w <= kCUs ? 1.15
+                                        : 0.5 * (double)((w + kCUs - 1) / kCUs) + (double)((w + kTileSlots - 1) / kTileSlots);
+            double c = std::max({cu * r * row, stages * 900, staged / 9.5e3});
+            if (np % 8) c = std::max(c, std::min(staged, all) / 6.3e3);
+            c += 2000.0 * (double)((w + kTileSlots - 1) / kTileSlots);
+            if (np > 1) c += 5000 + (double)w * b * b * 16 / 3e3;
+            if (c < (tb ? best : 0.95 * best)) {
+                best = c;
+                tb = b;
+                rows = r;
+                parts = np;
+            }
+        }
+    }
+    if (!tb) return false;
+    const int64_t tl = (n + tb - 1) / tb, tiles = tl * (tl + 1) / 2;
+    P.fine_tb = tb;
+    P.fine_parts = (int32_t)parts;
+    P.fine_rows = (int32_t)rows;
+    P.fine_row = sg[kSegHdr] + sg[1];
+    P.fine_k = (int32_t)k;
+    P.fine_beta = o.accumulate ? 1 : t.beta;
+    P.work_items = tiles * parts;
+    if (parts > 1) {
+        ++P.combine_tasks;
+        P.fine_off = P.ws_elems;
+        P.ws_elems += tiles * parts * tb * tb;
+    }
+    P.phases[0] = Phase{};
+    return true;
+}
+
 }  // namespace
 
 Plan build_plan(int64_t m, int64_t n, const PlanOptions& opt) {
@@ -876,6 +965,7 @@ Plan build_plan(int64_t m, int64_t n, const PlanOptions& opt) {
         Builder b(P);
         b.ata_node({Chunk{0, m}}, 0, n, 0, 0);
     }
+    if (fine_plan(P)) return P;
     split_k(P);
     if (opt.accumulate) {
         for (DevTask& t : P.tasks)

@@ -148,6 +148,10 @@ struct PlanOptions {
     // gemm_items or only syrk_items, 3 for the same bfloat16-pair phase (one
     // resident workgroup per CU) (0: never).
     int split_tail = 0;
+    // Fine tiles: a plan of one classical diagonal block over one row segment
+    // may run on 64 x 64 or 32 x 32 tiles (k_fine): 0 never, 1 FP64, 2 FP32.
+    // Its K range is split over workgroups only when split_target is set.
+    int fine = 0;
     // Reduced-precision leaves: the operand sums of the Strassen products
     // (operand-sum form) are converted into rows of a separate copy instead
     // of FP32 buffers (see DevOpSum).
@@ -200,6 +204,11 @@ struct Plan {
     // FP64 partial tiles of the K-split last round of one-term tile launches
     // (element offset in the workspace; -1 when no phase splits one)
     int64_t tile_tail_off = -1;
+    // Fine tiles (fine_tb 64 or 32; 0: not used, then the phases' items run):
+    // rows [fine_row, fine_row + fine_k) of the whole width n in fine_parts
+    // parts of fine_rows rows, partial tiles at fine_off of the workspace.
+    int32_t fine_tb = 0, fine_parts = 0, fine_rows = 0, fine_row = 0, fine_k = 0, fine_beta = 0;
+    int64_t fine_off = 0;
     int64_t opsum_elems = 0;  // operand-sum buffers, in elements of A's type
     int64_t lp_ops_rows = 0;  // reduced precision: rows of the operand copy
     int64_t lp_ops_k = 0;     // ... and its longest K

@@ -50,6 +50,15 @@ int64_t slab_rows_for(int64_t m, int64_t n) {
 // (exercises the failure path of the scheduler without a device).
 constexpr uint64_t kSimFailSeed = ATA_SERVER_SIM_FAIL_SEED;
 
+// Plans that join grouped launches.  Those run the SYRK tiles of each member
+// whole: plans with a K-split last round or fine tiles launch on their own.
+bool grouped_plan(const Plan& P) {
+    if (P.phases.size() != 1 || P.fine_tb) return false;
+    const Phase& ph = P.phases[0];
+    return ph.str_items.empty() && ph.tg_items.empty() && ph.gemm_items.empty() && ph.combines.empty() &&
+           ph.tail_items.empty();
+}
+
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 // First-fit allocator over offsets [0, size).
@@ -284,11 +293,7 @@ bool ata_server::admit(Req* q, int pass_stream) {
     ++st.admitted;
     if (sim()) return true;
     const Plan& P = q->plan->plan;
-    // a grouped launch runs the SYRK tiles of each member whole: plans with a
-    // K-split last round launch on their own
-    q->small = q->nslab == 1 && P.phases.size() == 1 && P.phases[0].str_items.empty() &&
-               P.phases[0].tg_items.empty() && P.phases[0].gemm_items.empty() && P.phases[0].combines.empty() &&
-               P.phases[0].tail_items.empty();
+    q->small = q->nslab == 1 && grouped_plan(P);
     q->stream = q->small ? pass_stream : (int)((pass + q->id) % streams.size());
     hipStream_t s = streams[q->stream];
     void* A = base + q->a.off;
@@ -586,7 +591,10 @@ int ata_server_submit(ata_server* srv, const ata_request* req, uint64_t* ticket)
         // the library's default depth rule for requests that leave it open;
         // the dtype class always (it selects the plan's split of short last rounds)
         const int pf = plan_flags(req->max_depth == -2 ? ATA_OPT_ADAPTIVE : 0, req->dtype);
-        rc = get_plan(rows, req->n, q->cutoff, q->variant, q->depth, pf, false, hp);
+        // a plan that joins grouped launches keeps the tiles those run
+        rc = get_plan(rows, req->n, q->cutoff, q->variant, q->depth, pf | kPlanNoFine, false, hp);
+        if (rc == ATA_OK && (q->nslab > 1 || !grouped_plan(hp->plan)))
+            rc = get_plan(rows, req->n, q->cutoff, q->variant, q->depth, pf, false, hp);
         if (rc != ATA_OK) return rc;
         q->L = ws_layout(rows, req->n, req->dtype, hp->plan.ws_elems, false, hp->plan.opsum_elems);
         q->plan = hp;
