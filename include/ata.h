@@ -413,8 +413,9 @@ int ata_potrf(void *C_lower, int64_t n, int dtype, int32_t *info, void *stream);
 /*
  * ata_potrs: solve L L^t X = B in place for the factor L from ata_potrf.
  *   B: row-major n x nrhs, row stride ldb >= nrhs, overwritten by X.  One
- *   launch per 64-row block for each of the forward and back substitutions;
- *   suited to a few right-hand sides (each is solved in turn inside a block).
+ *   launch for each of the forward and back substitutions and up to 128
+ *   right-hand sides.  Allocates a buffer of the solved values (about
+ *   2 n min(nrhs, 128) elements) stream-ordered on `stream`.
  */
 int ata_potrs(const void *L_lower, int64_t n, void *B, int64_t nrhs, int64_t ldb, int dtype, void *stream);
 

@@ -1,5 +1,5 @@
 // Consumers of the packed product on gfx950: the Cholesky factor of the
-// packed lower C, the two triangular solves with it, the right-hand side A^t b
+// packed lower C (the solves with it are in ata_trsv.hip), the right-hand side A^t b
 // of the normal equations and the product A X that applies the projection
 // A (A^t A)^-1 A^t (Section 1 names both as uses of A^t A); and the transpose
 // that gives the companion product A A^t.
@@ -8,8 +8,7 @@
 // i (i + 1) / 2 + j, so a row's entries left of the diagonal are contiguous.
 // The factorization is right-looking over 64-column blocks: per block, one
 // launch factors the diagonal block, one solves the rows below it, and one
-// MFMA launch applies the rank-64 update to the trailing lower triangle.  The
-// solves take one launch per 64-row block in each direction.
+// MFMA launch applies the rank-64 update to the trailing lower triangle.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -24,22 +23,11 @@ namespace {
 
 using detail::ProfScope;
 
-constexpr int NB = 64;  // block width of the factorization and the solves
+constexpr int NB = 64;  // block width of the factorization
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ int64_t pidx(int64_t i, int64_t j) { return i * (i + 1) / 2 + j; }
-
-// Value of v in lane src (uniform) for every lane, through scalar registers.
-__device__ __forceinline__ double lane_bcast(double v, int src) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ float lane_bcast(float v, int src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
-}
 
 // Orders the LDS accesses of one wave (no instruction needed: a wave's LDS
 // operations complete in order; this keeps the compiler from moving them).
@@ -308,160 +296,7 @@ __device__ __forceinline__ T wave_sum(T v) {
     return v;
 }
 
-constexpr int RC = 8;  // right-hand sides per pass of the solve updates
-
-// Stage the diagonal block d (width wd) of L in LDS, row stride NB + 1, with
-// the reciprocal of each diagonal entry in place of the entry.
-template <typename T>
-__device__ void stage_diag(const T* __restrict__ L, int64_t d0, int wd, T* ld) {
-    for (int e = threadIdx.x; e < NB * NB; e += blockDim.x) {
-        const int row = e >> 6, c = e & 63;
-        const T v = (row < wd && c <= row) ? L[pidx(d0 + row, d0 + c)] : T(0);
-        ld[row * (NB + 1) + c] = (c == row && row < wd) ? T(1) / v : v;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Forward substitution L Y = B, one launch per block (B row-major n x nrhs,
-// row stride ldb, overwritten by Y).  Launch k = -1 solves diagonal block 0.
-// Launch k >= 0 (block k already solved): workgroup b subtracts
-// L[block k+1+b rows][block k] Y_k from its 64 rows (one wave per row at a
-// time, lane = column of block k, wave-wide sums); workgroup 0 then solves
-// diagonal block k+1 with wave 0 (lane = row; column by column, each solved
-// value broadcast from its lane through scalar registers and scaled by the
-// staged reciprocal of the diagonal entry).
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_trsv_fwd(const T* __restrict__ L, int64_t n, T* __restrict__ B, int64_t nrhs,
-                                                  int64_t ldb, int64_t k) {
-    __shared__ T ld[NB * (NB + 1)];
-    __shared__ T ys[NB * RC];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    const int64_t tb = k + 1 + blockIdx.x;  // target block
-    const int64_t t0 = NB * tb;
-    if (k >= 0) {
-        const int64_t y0 = NB * k;
-        // this wave's 16 rows of L[.][block k], all loads in flight at once
-        T lv[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int64_t i = t0 + wv + 4 * u;
-            lv[u] = i < n ? L[pidx(i, y0 + lane)] : T(0);
-        }
-        for (int64_t r0 = 0; r0 < nrhs; r0 += RC) {
-            const int rc = (int)(nrhs - r0 < RC ? nrhs - r0 : RC);
-            __syncthreads();
-            for (int e = t; e < NB * RC; e += 256) {
-                const int c = e / RC, rr = e % RC;
-                ys[e] = rr < rc ? B[(y0 + c) * ldb + r0 + rr] : T(0);
-            }
-            __syncthreads();
-            for (int rr = 0; rr < rc; ++rr) {
-                const T y = ys[lane * RC + rr];
-#pragma unroll
-                for (int u = 0; u < 16; ++u) {
-                    const int64_t i = t0 + wv + 4 * u;
-                    const T s = wave_sum(lv[u] * y);
-                    if (lane == 0 && i < n) B[i * ldb + r0 + rr] -= s;
-                }
-            }
-        }
-    }
-    if (blockIdx.x != 0) return;
-    const int wd = (int)(n - t0 < NB ? n - t0 : NB);
-    __syncthreads();  // the rows just updated are read below
-    stage_diag(L, t0, wd, ld);
-    __syncthreads();
-    if (wv != 0) return;
-    for (int64_t r = 0; r < nrhs; ++r) {
-        T x = lane < wd ? B[(t0 + lane) * ldb + r] : T(0);
-        for (int c = 0; c < wd; ++c) {
-            const T xc = lane_bcast(x, c) * ld[c * (NB + 1) + c];
-            if (lane == c) x = xc;
-            if (lane > c) x -= ld[lane * (NB + 1) + c] * xc;
-        }
-        if (lane < wd) B[(t0 + lane) * ldb + r] = x;
-    }
-}
-
-// ---------------------------------------------------------------------------
-// Back substitution L^t X = Y, one launch per block, last block first.
-// Launch k = nblk solves the last diagonal block.  Launch k (block k solved)
-// has k workgroups: workgroup b subtracts L[block k][block k-1-b]^t X_k from
-// the rows of block k-1-b (lane = row of the target block, so the reads of a
-// row of L are contiguous; the four waves split the rows of block k and their
-// sums are added in a fixed order); workgroup 0 then solves diagonal block
-// k-1 with wave 0, last column first.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_trsv_bwd(const T* __restrict__ L, int64_t n, T* __restrict__ B, int64_t nrhs,
-                                                  int64_t ldb, int64_t k, int64_t nblk) {
-    __shared__ T ld[NB * (NB + 1)];
-    __shared__ T xs[NB * RC];
-    __shared__ T red[4 * NB * RC];
-    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
-    int64_t d;  // diagonal block solved by workgroup 0
-    if (k < nblk) {
-        const int64_t x0 = NB * k;
-        const int wk = (int)(n - x0 < NB ? n - x0 : NB);
-        const int64_t tb = k - 1 - blockIdx.x;
-        const int64_t c0 = NB * tb;
-        // this wave's 16 rows of L[block k][block tb], all loads in flight at once
-        T lv[16];
-#pragma unroll
-        for (int u = 0; u < 16; ++u) {
-            const int j = wv + 4 * u;
-            lv[u] = j < wk ? L[pidx(x0 + j, c0 + lane)] : T(0);
-        }
-        for (int64_t r0 = 0; r0 < nrhs; r0 += RC) {
-            const int rc = (int)(nrhs - r0 < RC ? nrhs - r0 : RC);
-            __syncthreads();
-            for (int e = t; e < NB * RC; e += 256) {
-                const int j = e / RC, rr = e % RC;
-                xs[e] = (j < wk && rr < rc) ? B[(x0 + j) * ldb + r0 + rr] : T(0);
-            }
-            __syncthreads();
-            T acc[RC];
-#pragma unroll
-            for (int rr = 0; rr < RC; ++rr) acc[rr] = T(0);
-#pragma unroll
-            for (int u = 0; u < 16; ++u) {
-                const int j = wv + 4 * u;  // xs rows past wk hold zeros
-#pragma unroll
-                for (int rr = 0; rr < RC; ++rr) acc[rr] += lv[u] * xs[j * RC + rr];
-            }
-#pragma unroll
-            for (int rr = 0; rr < RC; ++rr) red[(wv * NB + lane) * RC + rr] = acc[rr];
-            __syncthreads();
-            if (wv == 0) {
-                for (int rr = 0; rr < rc; ++rr) {
-                    const T s = ((red[lane * RC + rr] + red[(NB + lane) * RC + rr]) + red[(2 * NB + lane) * RC + rr]) +
-                                red[(3 * NB + lane) * RC + rr];
-                    B[(c0 + lane) * ldb + r0 + rr] -= s;
-                }
-            }
-        }
-        if (blockIdx.x != 0) return;
-        d = k - 1;
-    } else {
-        d = nblk - 1;
-    }
-    const int64_t d0 = NB * d;
-    const int wd = (int)(n - d0 < NB ? n - d0 : NB);
-    __syncthreads();
-    stage_diag(L, d0, wd, ld);
-    __syncthreads();
-    if (wv != 0) return;
-    for (int64_t r = 0; r < nrhs; ++r) {
-        T x = lane < wd ? B[(d0 + lane) * ldb + r] : T(0);
-        for (int c = wd - 1; c >= 0; --c) {
-            const T xc = lane_bcast(x, c) * ld[c * (NB + 1) + c];
-            if (lane == c) x = xc;
-            if (lane < c) x -= ld[c * (NB + 1) + lane] * xc;
-        }
-        if (lane < wd) B[(d0 + lane) * ldb + r] = x;
-    }
-}
+constexpr int RC = 8;  // right-hand sides per pass of A^t B and A X
 
 // ---------------------------------------------------------------------------
 // A^t B: partial sums over row chunks (workgroup = 256 columns x one chunk,
@@ -598,26 +433,6 @@ hipError_t potrf_t(T* C, int64_t n, int32_t* info, hipStream_t s, hipStream_t s2
 }
 
 template <typename T>
-hipError_t potrs_t(const T* L, int64_t n, T* B, int64_t nrhs, int64_t ldb, hipStream_t s) {
-    const int64_t nblk = (n + NB - 1) / NB;
-    for (int64_t k = -1; k < nblk - 1; ++k) {
-        const int64_t grid = k < 0 ? 1 : nblk - k - 1;
-        ProfScope ps(ATA_KERNEL_SOLVE, s);
-        hipLaunchKernelGGL(k_trsv_fwd<T>, dim3((unsigned)grid), dim3(256), 0, s, L, n, B, nrhs, ldb, k);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    for (int64_t k = nblk; k >= 1; --k) {
-        const int64_t grid = k == nblk ? 1 : k;
-        ProfScope ps(ATA_KERNEL_SOLVE, s);
-        hipLaunchKernelGGL(k_trsv_bwd<T>, dim3((unsigned)grid), dim3(256), 0, s, L, n, B, nrhs, ldb, k, nblk);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-}
-
-template <typename T>
 hipError_t atb_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int64_t nrhs, int64_t ldb, T* out,
                  int64_t ldo, double* part, int64_t chunks, hipStream_t s) {
     const int64_t rows = (m + chunks - 1) / chunks;
@@ -686,11 +501,6 @@ hipError_t launch_transpose(int elem_bytes, const void* A, int64_t m, int64_t n,
 hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, hipStream_t s, hipStream_t s2, hipEvent_t e,
                         hipEvent_t f) {
     return f32 ? potrf_t((float*)C, n, info, s, s2, e, f) : potrf_t((double*)C, n, info, s, s2, e, f);
-}
-
-hipError_t launch_potrs(bool f32, const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, hipStream_t s) {
-    return f32 ? potrs_t((const float*)L, n, (float*)B, nrhs, ldb, s)
-               : potrs_t((const double*)L, n, (double*)B, nrhs, ldb, s);
 }
 
 int64_t atb_chunks(int64_t m, int64_t n) {

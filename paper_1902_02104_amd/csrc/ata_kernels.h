@@ -142,8 +142,11 @@ hipError_t launch_convert(int mode, const float* x, int64_t count, void* out0, v
 // joined back into s before the call returns.
 hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, hipStream_t s, hipStream_t s2, hipEvent_t e,
                         hipEvent_t f);
-// L L^t X = B in place, B row-major n x nrhs with row stride ldb.
-hipError_t launch_potrs(bool f32, const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, hipStream_t s);
+// L L^t X = B in place, B row-major n x nrhs with row stride ldb (n, nrhs >= 1);
+// ws holds potrs_ws_bytes (256-byte aligned).
+size_t potrs_ws_bytes(bool f32, int64_t n, int64_t nrhs);
+hipError_t launch_potrs(bool f32, const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, void* ws,
+                        hipStream_t s);
 // out (m x nrhs, row stride ldo) = A X for A m x n (row stride lda) and X
 // n x nrhs (row stride ldx), FP64 sums.
 hipError_t launch_ax(bool f32, const void* A, int64_t m, int64_t n, int64_t lda, const void* X, int64_t nrhs,

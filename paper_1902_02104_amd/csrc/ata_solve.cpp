@@ -72,6 +72,17 @@ int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
     return e == hipSuccess ? ATA_OK : hip_fail(e);
 }
 
+int potrs_checked(const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, int dtype, hipStream_t s) {
+    if (n == 0 || nrhs == 0) return ATA_OK;
+    const bool f32 = dtype == ATA_F32;
+    void* ws = nullptr;
+    SOLVE_TRY(hipMallocAsync(&ws, potrs_ws_bytes(f32, n, nrhs), s));
+    hipError_t e = launch_potrs(f32, L, n, B, nrhs, ldb, ws, s);
+    const hipError_t e2 = hipFreeAsync(ws, s);
+    if (e == hipSuccess) e = e2;
+    return e == hipSuccess ? ATA_OK : hip_fail(e);
+}
+
 }  // namespace
 
 void atalib::detail::release_lookahead() {
@@ -114,9 +125,7 @@ int ata_potrs(const void* L_lower, int64_t n, void* B, int64_t nrhs, int64_t ldb
     if (misaligned(B, dtype)) return -3;
     if (n > kMaxOrder) return ATA_EUNSUPPORTED;
     if (!current_device_ok()) return ATA_EUNSUPPORTED;
-    if (n == 0 || nrhs == 0) return ATA_OK;
-    SOLVE_TRY(launch_potrs(dtype == ATA_F32, L_lower, n, B, nrhs, ldb, (hipStream_t)stream));
-    return ATA_OK;
+    return potrs_checked(L_lower, n, B, nrhs, ldb, dtype, (hipStream_t)stream);
 }
 
 int ata_atb(const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs, int64_t ldb, void* out,
@@ -165,10 +174,7 @@ int ata_normal_solve(const void* A, int64_t m, int64_t n, int64_t lda, const voi
     int rc = ata_ex(A, m, n, lda, C, dtype, cutoff, stream, nullptr, nullptr, 0);
     if (rc == ATA_OK) rc = potrf_checked(C, n, dtype, info, s);
     if (rc == ATA_OK) rc = atb_checked(A, m, n, lda, B, nrhs, ldb, X, ldx, dtype, s);
-    if (rc == ATA_OK && nrhs > 0) {
-        const hipError_t e = launch_potrs(dtype == ATA_F32, C, n, X, nrhs, ldx, s);
-        if (e != hipSuccess) rc = hip_fail(e);
-    }
+    if (rc == ATA_OK) rc = potrs_checked(C, n, X, nrhs, ldx, dtype, s);
     const hipError_t ef = hipFreeAsync(C, s);
     if (rc == ATA_OK && ef != hipSuccess) rc = hip_fail(ef);
     return rc;
