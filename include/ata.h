@@ -400,9 +400,9 @@ int ata_server_destroy(ata_server *srv);
  *
  * ata_potrf: Cholesky factor of the symmetric positive definite matrix in
  *   C_lower (n x n, packed), in place: on return C_lower holds L, lower
- *   triangular with positive diagonal and L L^t = C.  Right-looking in
- *   64-column blocks: per block one launch for the diagonal block, one for
- *   the rows below it and one MFMA launch for the trailing update.
+ *   triangular with positive diagonal and L L^t = C.  Panels of 256 columns:
+ *   one launch per 64 columns of a panel, then MFMA launches for the trailing
+ *   update.  Allocates 64 KB stream-ordered on `stream`.
  *   info: device int32 or NULL.  The call sets it to 0, and a kernel sets it
  *   to p + 1 for the first column p whose pivot is not positive (LAPACK's
  *   convention); L is then unspecified from column p on.  Read it after the

@@ -6,9 +6,15 @@
 //
 // Storage: row-major packed lower triangle, element (i, j), j <= i, at
 // i (i + 1) / 2 + j, so a row's entries left of the diagonal are contiguous.
-// The factorization is right-looking over 64-column blocks: per block, one
-// launch factors the diagonal block, one solves the rows below it, and one
-// MFMA launch applies the rank-64 update to the trailing lower triangle.
+//
+// The factorization has two levels of blocks.  Panels of NP = 256 columns are
+// factored 64 columns at a time, one launch per 64 columns (k_chol_panel);
+// after a panel, k_chol_syrk subtracts its product from the rest, 256 deep, so
+// that the trailing matrix is read and written once per 256 columns and its
+// tiles run at the rate of the FP64 product tiles.  Its first 256 columns (the
+// next panel) go first, on the caller's stream; the rest runs on a helper
+// stream beside the next panel's steps, which are a chain: every 64 columns
+// wait for the 64 before.
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
@@ -23,156 +29,502 @@ namespace {
 
 using detail::ProfScope;
 
-constexpr int NB = 64;  // block width of the factorization
+constexpr int NB = 64;       // columns of a step
+constexpr int NP = 4 * NB;   // columns of a panel
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
+typedef double d2_t __attribute__((ext_vector_type(2)));
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
 
 __device__ __forceinline__ int64_t pidx(int64_t i, int64_t j) { return i * (i + 1) / 2 + j; }
 
-// Orders the LDS accesses of one wave (no instruction needed: a wave's LDS
-// operations complete in order; this keeps the compiler from moving them).
+// Value of v in lane src (uniform) for every lane, through scalar registers.
+__device__ __forceinline__ double lane_bcast(double v, int src) {
+    const uint64_t b = __builtin_bit_cast(uint64_t, v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ float lane_bcast(float v, int src) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
+}
+
+// Orders the LDS accesses of one wave (they complete in order; this keeps the
+// compiler from moving them).
 __device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
-// ---------------------------------------------------------------------------
-// Diagonal block of the factorization at block column kb (width w <= 64), one
-// workgroup, in place.  Thread t owns column l = t & 63 and rows
-// i = (t >> 6) + 4 q (q < 16) of the block, and keeps a running copy of its
-// column's diagonal entry (updated by the same operation as the entry
-// itself), so the owners of step j take the pivot from their own copy.
-// Step j: the owners publish column j and 1 / pivot in LDS; after one
-// barrier every thread scales the entries it reads by 1 / pivot (as LAPACK's
-// unblocked factor scales the column) and applies the rank-one update to its
-// entries with selects.  A finished column is scaled when it is stored.  The column buffer
-// alternates between two halves by step parity: the barrier of step j + 1
-// separates the reads of step j from the writes of step j + 2.  A pivot that
-// is not positive is reported once through `info` (first failing column + 1,
-// LAPACK's convention); the factorization carries on with the resulting NaNs.
-// ---------------------------------------------------------------------------
+__device__ __forceinline__ void lds_copy16(rsrc_t r, void* lds, uint32_t voff, uint32_t soff) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
+}
+
 template <typename T>
-__global__ __launch_bounds__(256) void k_chol_diag(T* __restrict__ C, int64_t kb, int w, int32_t* __restrict__ info) {
-    __shared__ T col[2][NB];
-    __shared__ T rps[2];
-    // on the critical path while the helper stream's update fills the CUs:
-    // raise this wave's issue priority on its SIMD
-    __builtin_amdgcn_s_setprio(3);
-    const int t = threadIdx.x, l = t & 63, wv = t >> 6;
-    T d[16];
+__device__ __forceinline__ T buf_load(rsrc_t r, uint32_t off) {
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, 0));
+}
+typedef unsigned int u2_t __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ void buf_store(rsrc_t r, uint32_t off, T x) {
+    if constexpr (sizeof(T) == 8)
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u2_t, x), r, (int)off, 0, 0);
+    else
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, x), r, (int)off, 0, 0);
+}
+
+// r = 1 / sqrt(d) for d with pivot_in_range: the hardware estimate y (22 bits or
+// more) times the first terms of (1 - e)^(-1/2) in its residual e = 1 - d y^2,
+// one dependent step of four operations (the chain of columns pays it once
+// per column).  Exact where the result is a power of two.
+__device__ __forceinline__ double rsqrt_in_range(double d) {
+    const double y = __builtin_amdgcn_rsq(d);
+    const double e = __builtin_fma(-(d * y), y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(0.375, e, 0.5), y);
+}
+__device__ __forceinline__ float rsqrt_in_range(float d) {
+    const float y = __builtin_amdgcn_rsqf(d);
+    const float e = __builtin_fmaf(-(d * y), y, 1.0f);
+    return __builtin_fmaf(y * e, __builtin_fmaf(0.375f, e, 0.5f), y);
+}
+template <typename T>
+__device__ __forceinline__ bool pivot_in_range(T d) {
+    return sizeof(T) == 8 ? d > (T)0x1p-900 && d < (T)0x1p900 : d > (T)0x1p-100 && d < (T)0x1p100;
+}
+
+// ---------------------------------------------------------------------------
+// Products X Y^T of row slices of the packed matrix.  A stage holds 128 bytes
+// of each row (16 doubles or 32 floats of consecutive columns k): eight
+// 16-byte chunks, chunk c of row r at position c ^ swz(r), copied by buffer
+// loads that write LDS (eight rows an instruction; rows start on any multiple
+// of the element size).  A 128-bit operand read gives a lane VK consecutive k
+// of one row, one per MFMA; lane group g = lane >> 4 takes chunk 4 half + g,
+// so the MFMA for element e sums k = VK (4 half + g) + e over g, the same for
+// both operands.  swz sends the eight row pairs to eight positions, first
+// telling rows r and r + 2 apart by 64 bytes: the 16 rows of a right operand
+// and the 4 rows x 4 chunks of an FP64 left operand fall on distinct banks.
+// MFMA forms as in the product tiles: FP64 4 x 16 x 4 (left operand four rows
+// repeated), FP32 16 x 16 x 4.
+// ---------------------------------------------------------------------------
+constexpr int RB = 128;  // bytes of a staged row
+
+__device__ __forceinline__ int swz(int row) {
+    const int p = row >> 1;
+    return (p & 1) << 2 | (p & 2) | (p >> 2 & 1);
+}
+
+template <typename T>
+struct Mma;
+
+template <>
+struct Mma<double> {
+    static constexpr int RM = 4, NE = 1, VK = 2;  // rows of a block, elements per lane, k per 16 bytes
+    typedef double acc_t;
+    typedef d2_t vec_t;
+    __device__ static int arow(int lane) { return lane & 3; }
+    __device__ static int orow(int lane, int) { return lane >> 4; }
+    __device__ static double get(const acc_t& c, int) { return c; }
+    __device__ static void sub(acc_t& c, int, double v) { c = v - c; }
+    __device__ static acc_t zero() { return 0.0; }
+    __device__ static void mma(double a, double b, acc_t& c) { c = __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0); }
+};
+template <>
+struct Mma<float> {
+    static constexpr int RM = 16, NE = 4, VK = 4;
+    typedef f4_t acc_t;
+    typedef f4_t vec_t;
+    __device__ static int arow(int lane) { return lane & 15; }
+    __device__ static int orow(int lane, int e) { return 4 * (lane >> 4) + e; }
+    __device__ static float get(const acc_t& c, int e) { return c[e]; }
+    __device__ static void sub(acc_t& c, int e, float v) { c[e] = v - c[e]; }
+    __device__ static acc_t zero() { return f4_t{0.f, 0.f, 0.f, 0.f}; }
+    __device__ static void mma(float a, float b, acc_t& c) { c = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+};
+
+// acc (NR row blocks x NC column blocks of 16) += X Y^T over one stage; xa
+// (first half of the row blocks), xb (second half) and y point to the first
+// staged rows of this wave's operands (multiples of 16).
+template <typename T, int NR, int NC>
+__device__ __forceinline__ void mma_stage(const char* xa, const char* xb, const char* y, int lane,
+                                          typename Mma<T>::acc_t (&acc)[NR][NC]) {
+    typedef Mma<T> M;
+    typedef typename M::vec_t V;
+    const int g = lane >> 4;
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int i = wv + 4 * q;
-        d[q] = (i < w && l <= i) ? C[pidx(kb + i, kb + l)] : T(0);
-    }
-    T dd = l < w ? C[pidx(kb + l, kb + l)] : T(1);
-    T myrp = T(1), mypiv = T(0);  // this thread's column: 1 / pivot and pivot
-    for (int j = 0; j < w; ++j) {
-        T* cb = col[j & 1];
-        if (l == j) {
-            // the owners publish column j unscaled with 1 / pivot; each reader
-            // forms the scaled entries it needs (the same products), and a
-            // column is scaled in place only when it is stored
-            mypiv = sqrt(dd);
-            myrp = T(1) / mypiv;
-            if (wv == 0 && !(dd > T(0)) && info) atomicCAS(info, 0, (int32_t)(kb + j + 1));
+    for (int half = 0; half < 2; ++half) {
+        constexpr int GR = NR / 2 < 8 ? NR / 2 : 8;  // row blocks read at a time
+        V b[NC];
 #pragma unroll
-            for (int q = 0; q < 16; ++q) cb[wv + 4 * q] = d[q];
-            if (wv == 0) rps[j & 1] = myrp;
+        for (int c = 0; c < NC; ++c) {
+            const int row = 16 * c + (lane & 15);
+            b[c] = *(const V*)(y + row * RB + 16 * ((4 * half + g) ^ swz(row)));
         }
-        __syncthreads();
-        const bool act = l > j && l < w;
-        const T rpj = rps[j & 1];
-        const T lj = cb[l] * rpj;
 #pragma unroll
-        for (int q = 0; q < 16; ++q) {
-            const int i = wv + 4 * q;
-            const T v = d[q] - (cb[i] * rpj) * lj;
-            d[q] = (act && i >= l) ? v : d[q];
+        for (int r0 = 0; r0 < NR; r0 += GR) {
+            V a[GR];
+#pragma unroll
+            for (int r = 0; r < GR; ++r) {
+                const int row = M::RM * ((r0 + r) % (NR / 2)) + M::arow(lane);
+                a[r] = *(const V*)((r0 < NR / 2 ? xa : xb) + row * RB + 16 * ((4 * half + g) ^ swz(row)));
+            }
+#pragma unroll
+            for (int e = 0; e < M::VK; ++e)
+#pragma unroll
+                for (int r = 0; r < GR; ++r)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c) M::mma(a[r][e], b[c][e], acc[r0 + r][c]);
         }
-        if (act) dd -= lj * lj;
-    }
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int i = wv + 4 * q;
-        if (i < w && l <= i) C[pidx(kb + i, kb + l)] = i > l ? d[q] * myrp : (i == l ? mypiv : d[q]);
     }
 }
 
 // ---------------------------------------------------------------------------
-// Rows below the diagonal block: L21 = C21 L11^-t for rows
-// R0 = kb + w + 64 b ... R0 + 63 (workgroup b), with the factored L11 staged
-// in LDS.  Thread t owns column l = t & 63 and rows i = (t >> 6) + 4 q; each
-// step scales column j (times the staged 1 / L11[j][j]) and subtracts its
-// multiples from the later columns, the order the diagonal block uses.
+// One step: columns [kb, kb + w), w <= 64, of a panel that starts at column
+// pb.  Workgroup b owns 64 rows below the diagonal block, from kb + 64 + 64 b.
+// Every workgroup also factors the diagonal block (a few microseconds, against
+// a launch of its own plus a trip through memory), so a step is one launch:
+//  1. The 128 rows (diagonal block, own rows) minus the panel's columns left
+//     of kb, by MFMA (a wave: 32 rows x 64 columns), left in registers.
+//  2. Sixteen columns at a time.  Wave 0 factors the diagonal block's part
+//     with a row per lane; waves 0 and 1 then subtract its product from the
+//     rest of the diagonal block.  Beside that chain, one step behind, waves 2
+//     and 3 solve the own rows for the 16 columns (a row per lane) and
+//     subtract their product from the columns to the right.
+//  3. The rows are stored.  The diagonal block goes to `diag` (64 x 64), since
+//     other workgroups may still read it in C; the next step's workgroup 0
+//     puts it in place (`prev`, null for the first step).  A last block
+//     without rows below is stored at once.
+// A pivot that is not positive is reported once through `info` (first failing
+// column + 1, LAPACK's convention); the factorization carries on.
+// LDS 79 KB (FP64) and 256 registers: beside one workgroup of the update on the
+// same CU.
+// Measured alone (MI355X): see potrf_t.
 // ---------------------------------------------------------------------------
+// Row stride of the factored columns in LDS: 16 rows apart by distinct 16-byte
+// bank groups, for 128-bit reads by rows.
 template <typename T>
-__global__ __launch_bounds__(256) void k_chol_rows(T* __restrict__ C, int64_t n, int64_t kb, int w) {
-    __shared__ T ld[NB * (NB + 1)];
-    __shared__ T col[NB];
-    __shared__ T rcp[NB];
-    __builtin_amdgcn_s_setprio(3);  // critical path, as in k_chol_diag
-    const int t = threadIdx.x, l = t & 63, wv = t >> 6;
-    const int64_t R0 = kb + w + (int64_t)NB * blockIdx.x;
-    for (int e = t; e < NB * NB; e += 256) {
-        const int row = e >> 6, c = e & 63;
-        ld[row * (NB + 1) + c] = (row < w && c <= row) ? C[pidx(kb + row, kb + c)] : T(0);
-    }
-    if (t < w) rcp[t] = T(1) / C[pidx(kb + t, kb + t)];
-    T r[16];
+constexpr int kLB = sizeof(T) == 8 ? 66 : 68;
+constexpr int SX = 17;  // row stride of the diagonal block's 16 columns handed to the row lanes
+
+// Columns [16 s, 16 s + 16) of the diagonal block, lane = row.  The chain from
+// one pivot to the next runs on values every lane holds: with X = D[c+1][c]
+// and P = D[c+1][c+1] broadcast a column ahead, the next pivot is P - (X r)^2,
+// the operation row c + 1 does itself.  The multipliers of columns beyond the
+// next two pass through LDS (mb, two columns of 64) and are used a column
+// later, off that chain.  A scaled pivot is its root, to an ulp.  Returns
+// false if a pivot is out of the range of rsqrt_in_range.
+template <typename T>
+__device__ __forceinline__ bool factor16(T (&d)[16], T* mb, int b0, int lane) {
+    typedef T v2_t __attribute__((ext_vector_type(2)));
+    T piv = lane_bcast(d[0], b0), X = lane_bcast(d[0], b0 + 1), P = lane_bcast(d[1], b0 + 1);
+    T r = rsqrt_in_range(piv);
+    bool ok = pivot_in_range(piv);
+    v2_t mv[7];  // multipliers 2.. of the column before, read while it was scaled
 #pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int i = wv + 4 * q;
-        r[q] = (R0 + i < n && l < w) ? C[pidx(R0 + i, kb + l)] : T(0);
+    for (int c = 0; c < 16; ++c) {
+        // the scheduler fills the chain to the next root with updates; keeping
+        // it from reaching further bounds the registers
+        __builtin_amdgcn_sched_barrier(0);
+        const T rc = r;
+        // the column before, for the columns its multipliers came through LDS
+        if (c >= 1 && c < 14) {
+#pragma unroll
+            for (int k = 2; k < 16; ++k)
+                if (k >= c + 2) d[k] -= d[c - 1] * mv[k / 2 - 1][k & 1];
+        }
+        d[c] *= rc;
+        if (c < 13) mb[(c & 1) * NB + lane] = d[c];
+        if (c < 15) {
+            const T l = X * rc;
+            piv = P - l * l;
+            r = rsqrt_in_range(piv);
+            ok = ok && pivot_in_range(piv);
+            d[c + 1] -= d[c] * l;
+        }
+        if (c < 14) {
+            d[c + 2] -= d[c] * lane_bcast(d[c], b0 + c + 2);
+            X = lane_bcast(d[c + 1], b0 + c + 2);
+            P = lane_bcast(d[c + 2], b0 + c + 2);
+        }
+        if (c < 13) {
+            wave_lds_fence();
+#pragma unroll
+            for (int k = 2; k < 16; k += 2)
+                if (k + 1 >= c + 3) mv[k / 2 - 1] = *(const v2_t*)&mb[(c & 1) * NB + b0 + k];
+        }
+    }
+    return ok;
+}
+
+// The same columns for any pivot, with the plain square root and reciprocal,
+// in place in LDS (sx, a row per lane); reports the first pivot that is not
+// positive through info.
+template <typename T>
+__device__ __noinline__ void factor16_any(T* sx, int b0, int lane, int32_t* info, int64_t kb, int w) {
+#pragma clang loop unroll(disable)
+    for (int c = 0; c < 16; ++c) {
+        const T piv = sx[(b0 + c) * SX + c];
+        const T root = sqrt(piv), r = T(1) / root;
+        if (info && !(piv > T(0)) && b0 + c < w && lane == 0) atomicCAS(info, 0, (int32_t)(kb + b0 + c + 1));
+        const T x = lane == b0 + c ? root : sx[lane * SX + c] * r;
+        wave_lds_fence();
+        sx[lane * SX + c] = x;
+        wave_lds_fence();
+#pragma clang loop unroll(disable)
+        for (int k = c + 1; k < 16; ++k) {
+            const T m = sx[(b0 + k) * SX + c];
+            sx[lane * SX + k] -= x * m;
+        }
+        wave_lds_fence();
+    }
+}
+
+// Workgroup barrier for LDS data alone.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+template <typename T>
+__global__ __launch_bounds__(256, 2) void k_chol_panel(T* __restrict__ C, int64_t n, int64_t pb, int64_t kb, int w,
+                                                    int32_t* __restrict__ info, T* __restrict__ diag,
+                                                    const T* __restrict__ prev) {
+    typedef Mma<T> M;
+    typedef typename M::vec_t V;
+    constexpr int NR = 32 / M::RM, NE = M::NE, KS = RB / (int)sizeof(T), LB = kLB<T>;
+    constexpr int NBUF = sizeof(T) == 8 ? 4 : 2;  // stages in flight
+    constexpr int NJ = 4 / M::VK;                 // 128-bit reads per row of 16 columns and lane group
+    __shared__ __attribute__((aligned(16))) T lb[2 * NB * LB];
+    __shared__ T sx[NB * SX];
+    __shared__ __attribute__((aligned(16))) T mb[2 * NB];
+    __shared__ T rw[2][16];  // reciprocals of the 16 pivots, for each own wave
+    static_assert(NBUF * 128 * RB <= sizeof(lb), "stages of 128 rows");
+    // on the critical path while the helper stream's update fills the CUs
+    __builtin_amdgcn_s_setprio(3);
+    const int t = threadIdx.x, lane = t & 63, g = lane >> 4;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t r0 = kb + NB + (int64_t)NB * blockIdx.x;  // first own row
+    const bool own = r0 < n;
+    // This wave's two groups of 16 of the 128 rows.  Waves 0 and 1 share the
+    // lower triangle of the diagonal block: groups 0 and 3, 1 and 2.
+    const int ga = wv < 2 ? wv : 2 * wv, gb = wv < 2 ? 3 - wv : 2 * wv + 1;
+
+    // C values of this wave's rows
+    typename M::acc_t v[NR][4];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int row = 16 * (r < NR / 2 ? ga : gb) + M::RM * (r % (NR / 2)) + M::orow(lane, e);
+                const int64_t i = row < NB ? kb + row : r0 + (row - NB), j = kb + 16 * c + (lane & 15);
+                // a short last block is continued by the identity
+                T x = i == j ? T(1) : T(0);
+                if (i < n && j <= i) x = C[pidx(i, j)];
+                if constexpr (NE == 1)
+                    v[r][c] = x;
+                else
+                    v[r][c][e] = x;
+            }
+    if (kb > pb) {
+        // minus the product with the panel's columns [pb, kb)
+        char* const st = (char*)lb;
+        const int64_t b0 = wv < 2 ? kb : r0;  // rows this wave copies: 32 of the 128
+        const int64_t first = b0 < n ? b0 : n - 1;
+        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(C + pidx(first, pb), (short)0, 0x7fffffff, 0x00020000);
+        uint32_t off[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int row = 32 * (wv & 1) + 8 * i + (lane >> 3);  // of the 64 rows from b0
+            const int64_t gi = b0 + row < n ? b0 + row : n - 1;
+            off[i] = (uint32_t)((pidx(gi, pb) - pidx(first, pb)) * (int64_t)sizeof(T)) +
+                     16u * (uint32_t)((lane & 7) ^ swz(row));
+        }
+        auto copy = [&](int k, int buf) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                lds_copy16(rs, st + (buf * 128 + 32 * wv + 8 * i) * RB, off[i], (uint32_t)(k * RB));
+        };
+        typename M::acc_t acc[NR][4];
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[r][c] = M::zero();
+        const int ns = (int)(kb - pb) / KS;  // a multiple of 4 (FP64) or 2 (FP32)
+#pragma unroll
+        for (int k = 0; k < NBUF - 1; ++k) copy(k, k);
+        for (int k = 0; k < ns; ++k) {
+            // this wave's copies of stage k have landed (four per stage; up
+            // to two later stages stay in flight)
+            if (NBUF == 4 && k + 2 < ns)
+                asm volatile("s_waitcnt vmcnt(8)" ::: "memory");
+            else if (NBUF == 4 && k + 1 < ns)
+                asm volatile("s_waitcnt vmcnt(4)" ::: "memory");
+            else
+                asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            // everyone's have, and the oldest buffer is read (a bare barrier:
+            // a fence would wait for the later stages too)
+            lds_barrier();
+            if (k + NBUF - 1 < ns) copy(k + NBUF - 1, (k + NBUF - 1) % NBUF);
+            const char* x = st + (k % NBUF) * 128 * RB;
+            mma_stage<T, NR, 4>(x + 16 * ga * RB, x + 16 * gb * RB, x, lane, acc);
+        }
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) v[r][c] -= acc[r][c];
+        if (w < NB) {
+            // rows past the end: the identity again (their copies repeat the last row)
+#pragma unroll
+            for (int r = 0; r < NR; ++r)
+#pragma unroll
+                for (int e = 0; e < NE; ++e)
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) {
+                        const int row = 16 * (r < NR / 2 ? ga : gb) + M::RM * (r % (NR / 2)) + M::orow(lane, e);
+                        const T x = row == 16 * c + (lane & 15) ? T(1) : T(0);
+                        if constexpr (NE == 1)
+                            v[r][c] = row >= w ? x : v[r][c];
+                        else
+                            v[r][c][e] = row >= w ? x : v[r][c][e];
+                    }
+        }
+        lds_barrier();  // the stages are read: lb is free
+    }
+
+    // columns [16 s, 16 s + 16) of this wave's rows to p (row stride st, first
+    // of the rows row0)
+    auto put = [&](int s, T* p, int st, int row0) {
+#pragma unroll
+        for (int r = 0; r < NR; ++r)
+#pragma unroll
+            for (int e = 0; e < NE; ++e) {
+                const int row = 16 * (r < NR / 2 ? ga : gb) + M::RM * (r % (NR / 2)) + M::orow(lane, e);
+                p[(row - row0) * st + (lane & 15)] = M::get(v[r][s], e);
+            }
+    };
+    // The factored 16 columns from 16 s: minus the product of this wave's rows
+    // with rows 16 c .. of the diagonal block, in its column blocks c > s (of
+    // the diagonal block the lower ones).  Lane group g takes the k of one
+    // 128-bit read, the same for both operands.
+    auto update = [&](int s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int gr = h == 0 ? ga : gb;
+            V a[NJ][NR / 2];
+#pragma unroll
+            for (int j = 0; j < NJ; ++j)
+#pragma unroll
+                for (int r = 0; r < NR / 2; ++r)
+                    a[j][r] = -*(const V*)&lb[(16 * gr + M::RM * r + M::arow(lane)) * LB + 16 * s + (4 * j + g) * M::VK];
+#pragma unroll
+            for (int c = 1; c < 4; ++c)
+                if (c > s && c <= gr)
+#pragma unroll
+                    for (int j = 0; j < NJ; ++j) {
+                        const V b = *(const V*)&lb[(16 * c + (lane & 15)) * LB + 16 * s + (4 * j + g) * M::VK];
+#pragma unroll
+                        for (int e = 0; e < M::VK; ++e)
+#pragma unroll
+                            for (int r = 0; r < NR / 2; ++r) M::mma(a[j][r][e], b[e], v[h * (NR / 2) + r][c]);
+                    }
+        }
+    };
+    if (wv < 2) {
+        put(0, sx, SX, 0);
+        lds_barrier();
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            if (wv == 0) {
+                T d[16];
+#pragma unroll
+                for (int c = 0; c < 16; ++c) d[c] = sx[lane * SX + c];
+                if (!factor16<T>(d, mb, 16 * s, lane)) {
+                    factor16_any<T>(sx, 16 * s, lane, blockIdx.x == 0 ? info : nullptr, kb, w);
+#pragma unroll
+                    for (int c = 0; c < 16; ++c) d[c] = sx[lane * SX + c];
+                }
+#pragma unroll
+                for (int c = 0; c < 16; ++c) lb[lane * LB + 16 * s + c] = d[c];
+            }
+            lds_barrier();
+            if (s < 3) {
+                update(s);
+                put(s + 1, sx, SX, 0);
+            }
+            lds_barrier();
+        }
+    } else {
+        lds_barrier();
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            lds_barrier();
+            lds_barrier();
+            // lanes l and l + 32 both hold own row 32 (wv - 2) + (l & 31)
+            put(s, lb + NB * LB + 16 * s, LB, NB);
+            if (lane < 16) rw[wv - 2][lane] = T(1) / lb[(16 * s + lane) * LB + 16 * s + lane];
+            wave_lds_fence();
+            T* const row = &lb[(NB + 32 * (wv - 2) + (lane & 31)) * LB + 16 * s];
+            T o[16];
+#pragma unroll
+            for (int c = 0; c < 16; c += M::VK) {
+                const V x = *(const V*)&row[c];
+#pragma unroll
+                for (int e = 0; e < M::VK; ++e) o[c + e] = x[e];
+            }
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const T* lk = &lb[(16 * s + k) * LB + 16 * s];
+#pragma unroll
+                for (int c = 0; c < 16; c += M::VK)
+                    if (c < k) {
+                        const V m = *(const V*)&lk[c];
+#pragma unroll
+                        for (int e = 0; e < M::VK; ++e)
+                            if (c + e < k) o[k] -= o[c + e] * m[e];
+                    }
+                o[k] *= rw[wv - 2][k];
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int c = 0; c < 16; c += M::VK) {
+                V x;
+#pragma unroll
+                for (int e = 0; e < M::VK; ++e) x[e] = o[c + e];
+                *(V*)&row[c] = x;
+            }
+            wave_lds_fence();
+            if (s < 3) update(s);
+        }
     }
     __syncthreads();
-    // The rows of a wave (i = wv + 4 q) depend only on each other and on L11,
-    // and the column entries col[wv + 4 q] are written and read by that wave
-    // alone: the steps need wave-level ordering only.
-    // The owner lane publishes its column unscaled; readers scale by the
-    // staged 1 / L11[j][j] (the same products), and a column is scaled when
-    // it is stored.
-    for (int j = 0; j < w; ++j) {
-        if (l == j) {
-#pragma unroll
-            for (int q = 0; q < 16; ++q) col[wv + 4 * q] = r[q];
+
+    // rows to memory, a row per wave and pass
+    if (own)
+        for (int r = wv; r < NB; r += 4)
+            if (r0 + r < n) C[pidx(r0 + r, kb + lane)] = lb[(NB + r) * LB + lane];
+    if (blockIdx.x == 0) {
+        for (int r = wv; r < w; r += 4) {
+            const T x = lb[r * LB + lane];
+            if (own)
+                diag[r * NB + lane] = x;
+            else if (lane <= r)
+                C[pidx(kb + r, kb + lane)] = x;
+            if (prev && lane <= r) C[pidx(kb - NB + r, kb - NB + lane)] = prev[r * NB + lane];
         }
-        wave_lds_fence();
-        if (l > j && l < w) {
-            const T lj = ld[l * (NB + 1) + j];
-            const T rj = rcp[j];
-#pragma unroll
-            for (int q = 0; q < 16; ++q) r[q] -= (col[wv + 4 * q] * rj) * lj;
-        }
-        wave_lds_fence();
-    }
-    const T rl = l < w ? rcp[l] : T(0);
-#pragma unroll
-    for (int q = 0; q < 16; ++q) {
-        const int i = wv + 4 * q;
-        if (R0 + i < n && l < w) C[pidx(R0 + i, kb + l)] = r[q] * rl;
+        if (prev)  // rows of the previous block beyond a short one
+            for (int r = w + wv; r < NB; r += 4)
+                if (lane <= r) C[pidx(kb - NB + r, kb - NB + lane)] = prev[r * NB + lane];
     }
 }
 
 // ---------------------------------------------------------------------------
-// Trailing update: C[i][j] -= sum_{k < w} L[i][kb + k] L[j][kb + k] for
-// s <= j <= i < n, s = kb + w, over the 64 x 64 tiles (ti, tj), tj <= ti, of
-// the trailing lower triangle.  part 0 takes every tile, part 1 only the
-// first tile column (tj = 0: the next diagonal block and the rows below it),
-// part 2 the others; the tile comes from the linear workgroup index.  Each
-// wave first loads its quarter of the C tile (those loads complete under the
-// staging and the MFMAs), then both panel slices are staged transposed in
-// LDS ([k][row], row stride 68: 4 mod 16 doubles, so the broadcast operand
-// reads of the FP64 form fall on distinct banks) and four waves each form a
-// 32 x 32 quarter on MFMA; on a diagonal tile the quarter above the diagonal
-// is skipped.
-//   FP64: v_mfma_f64_4x4x4f64 with the left operand broadcast to the four
-//         blocks, a 4 x 16 x 4 product: left lane l = X[row l & 3][k l >> 4],
-//         right lane l = Y[k l >> 4][col l & 15], result lane l =
-//         D[row l >> 4][col l & 15].
-//   FP32: v_mfma_f32_16x16x4f32: left lane l = X[row l & 15][k l >> 4],
-//         right as above, result element e of lane l = D[row 4 (l >> 4) + e]
-//         [col l & 15].
+// Trailing update after the panel [pb, pb + NP): C[i][j] -= sum over the panel
+// of L[i][k] L[j][k] for s0 <= j <= i < n, s0 = pb + NP, on UT x UT tiles from
+// s0.  part 0 takes every tile, part 1 the first NP columns (the next panel),
+// part 2 the others.  Four waves of UT/2 x UT/2, one stage ahead; the sum is
+// formed first and subtracted once.  UT = 128 (two workgroups per CU) reads
+// each operand half as often; UT = 64 gives four times the workgroups, each
+// done in a quarter of the time: for the parts on the chain and for trailing
+// matrices of few tiles.
 // ---------------------------------------------------------------------------
-constexpr int UP = NB + 4;
-
 // Row a and column c of linear index b in a lower triangle of tiles.
 __device__ __forceinline__ void tri_decode(int64_t b, int64_t& a, int64_t& c) {
     a = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
@@ -181,110 +533,124 @@ __device__ __forceinline__ void tri_decode(int64_t b, int64_t& a, int64_t& c) {
     c = b - a * (a + 1) / 2;
 }
 
-template <typename T>
-__global__ __launch_bounds__(256, 2) void k_chol_update(T* __restrict__ C, int64_t n, int64_t kb, int w, int tiles,
-                                                        int part) {
-    __shared__ T Pi[NB * UP];
-    __shared__ T Pj[NB * UP];
+template <typename T, int UT>
+__global__ __launch_bounds__(256, UT == 128 ? 2 : 4) void k_chol_syrk(T* __restrict__ C, int64_t n, int64_t pb,
+                                                                    int part) {
+    typedef Mma<T> M;
+    constexpr int WT = UT / 2, NR = WT / M::RM, NC = WT / 16, NE = M::NE, KS = RB / (int)sizeof(T);
+    constexpr int NPT = NP / UT;  // tile columns of the next panel
+    constexpr int NI = UT / 16;   // copies of a wave per stage (eight rows each)
+    __shared__ __attribute__((aligned(16))) char st[2][2 * UT * RB];
     int64_t ti, tj;
     if (part == 1) {
-        ti = blockIdx.x;
-        tj = 0;
-    } else if (part == 2) {
-        tri_decode(blockIdx.x, ti, tj);
-        ++ti;
-        ++tj;
+        // the first NPT tile columns: their triangle, then whole rows of NPT
+        const int64_t b = blockIdx.x, tri = NPT * (NPT + 1) / 2;
+        if (b < tri) {
+            tri_decode(b, ti, tj);
+        } else {
+            ti = NPT + (b - tri) / NPT;
+            tj = (b - tri) % NPT;
+        }
     } else {
         tri_decode(blockIdx.x, ti, tj);
+        if (part == 2) {
+            ti += NPT;
+            tj += NPT;
+        }
     }
-    if (ti >= tiles) return;
-    const int64_t s = kb + w;
-    const int64_t r0 = s + NB * ti, c0 = s + NB * tj;
-    const bool diag = ti == tj;
+    const int64_t s0 = pb + NP, r0 = s0 + UT * ti, c0 = s0 + UT * tj;
+    const bool dg = ti == tj;
     const int t = threadIdx.x, lane = t & 63;
     const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
     const int wr = wv >> 1, wc = wv & 1;
-    const bool active = !(diag && wr < wc);
-    // C values of this wave's quarter, in the result layout of the MFMA form
-    constexpr int NV = 16;
-    T cv[NV];
+
+    // this wave's copies: half of the left rows (waves 0, 1) or right rows
+    const int64_t b0 = wv < 2 ? r0 : c0;
+    const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(C + pidx(b0, pb), (short)0, 0x7fffffff, 0x00020000);
+    uint32_t off[NI];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        int64_t i, j;
-        if constexpr (sizeof(T) == 8) {
-            i = r0 + 32 * wr + 4 * (v >> 1) + (lane >> 4);
-            j = c0 + 32 * wc + 16 * (v & 1) + (lane & 15);
-        } else {
-            i = r0 + 32 * wr + 16 * (v >> 3) + 4 * (lane >> 4) + (v & 3);
-            j = c0 + 32 * wc + 16 * ((v >> 2) & 1) + (lane & 15);
-        }
-        cv[v] = (active && i < n && j <= i) ? C[pidx(i, j)] : T(0);
+    for (int i = 0; i < NI; ++i) {
+        const int row = WT * (wv & 1) + 8 * i + (lane >> 3);
+        const int64_t gi = b0 + row < n ? b0 + row : n - 1;
+        off[i] = (uint32_t)((pidx(gi, pb) - pidx(b0, pb)) * (int64_t)sizeof(T)) + 16u * (uint32_t)((lane & 7) ^ swz(row));
     }
-    // panel slices: all 32 loads of a thread in flight before the LDS stores
-    // (row (t >> 6) + 4 u, k = lane: one 512-byte row segment per wave load)
-    T pv[16], qv[16];
+    const bool copies = wv < 2 || !dg;
+    auto copy = [&](int k, int buf) {
+        if (!copies) return;
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const int row = (t >> 6) + 4 * u;
-        const int64_t gi = r0 + row, gj = c0 + row;
-        pv[u] = (gi < n && lane < w) ? C[pidx(gi, kb + lane)] : T(0);
-        qv[u] = (!diag && gj < n && lane < w) ? C[pidx(gj, kb + lane)] : T(0);
+        for (int i = 0; i < NI; ++i)
+            lds_copy16(rs, &st[buf][(UT * (wv >> 1) + WT * (wv & 1) + 8 * i) * RB], off[i], (uint32_t)(k * RB));
+    };
+    typename M::acc_t acc[NR][NC];
+#pragma unroll
+    for (int r = 0; r < NR; ++r)
+#pragma unroll
+        for (int c = 0; c < NC; ++c) acc[r][c] = M::zero();
+    const bool live = !(dg && wr < wc);  // above the diagonal: copies only
+    copy(0, 0);
+#pragma clang loop unroll(disable)
+    for (int k = 0; k < NP / KS; ++k) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        if (k + 1 < NP / KS) copy(k + 1, (k + 1) & 1);
+        if (!live) continue;
+        __builtin_amdgcn_s_setprio(1);
+        const char* x = st[k & 1] + WT * wr * RB;
+        mma_stage<T, NR, NC>(x, x + WT / 2 * RB, st[k & 1] + ((dg ? 0 : UT) + WT * wc) * RB, lane, acc);
+        __builtin_amdgcn_s_setprio(0);
     }
+    if (!live) return;
+    // C in batches of up to 32 values, the loads of a batch in flight
+    // together.  Row k of this wave starts k Ru + k (k + 1) / 2 elements after
+    // its first row Ru.
+    constexpr int GR = NR < 8 / NE ? NR : 8 / NE;
+    const int64_t Ru = r0 + WT * wr, cu = c0 + WT * wc;
+    const rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(C + pidx(Ru, cu), (short)0, 0x7fffffff, 0x00020000);
+    const bool inside = !dg && r0 + UT <= n;
+    uint32_t l0 = lane & 15;
+    asm volatile("" : "+v"(l0));  // the offsets are formed here, not kept through the loop
+    auto at = [&](int r, int e) {
+        const uint32_t k = M::RM * r + M::orow(lane, e);
+        return (k * (uint32_t)Ru + k * (k + 1) / 2 + l0) * (uint32_t)sizeof(T);
+    };
+    auto in = [&](int r, int e, int c) {
+        const int64_t i = Ru + M::RM * r + M::orow(lane, e);
+        return i < n && cu + 16 * c + (int64_t)l0 <= i;
+    };
 #pragma unroll
-    for (int u = 0; u < 16; ++u) {
-        const int row = (t >> 6) + 4 * u;
-        Pi[lane * UP + row] = pv[u];
-        if (!diag) Pj[lane * UP + row] = qv[u];
-    }
-    __syncthreads();
-    if (!active) return;
-    const T* Y = diag ? Pi : Pj;
-    if constexpr (sizeof(T) == 8) {
-        double acc[8][2];
+    for (int q = 0; q < NR; q += GR) {
+        T cv[GR][NE][NC];
+        if (inside) {
 #pragma unroll
-        for (int g = 0; g < 8; ++g) acc[g][0] = acc[g][1] = 0.0;
-        for (int k0 = 0; k0 < NB; k0 += 4) {
-            const int kr = (k0 + (lane >> 4)) * UP;
-            double a[8], bb[2];
+            for (int r = 0; r < GR; ++r)
 #pragma unroll
-            for (int g = 0; g < 8; ++g) a[g] = Pi[kr + 32 * wr + 4 * g + (lane & 3)];
+                for (int e = 0; e < NE; ++e)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) bb[h] = Y[kr + 32 * wc + 16 * h + (lane & 15)];
+                    for (int c = 0; c < NC; ++c) cv[r][e][c] = buf_load<T>(rc, at(q + r, e) + 16u * c * (uint32_t)sizeof(T));
 #pragma unroll
-            for (int g = 0; g < 8; ++g)
+            for (int r = 0; r < GR; ++r)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) acc[g][h] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[g], bb[h], acc[g][h], 0, 0, 0);
+                for (int e = 0; e < NE; ++e)
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        buf_store<T>(rc, at(q + r, e) + 16u * c * (uint32_t)sizeof(T), cv[r][e][c] - M::get(acc[q + r][c], e));
+            continue;
         }
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int64_t i = r0 + 32 * wr + 4 * (v >> 1) + (lane >> 4);
-            const int64_t j = c0 + 32 * wc + 16 * (v & 1) + (lane & 15);
-            if (i < n && j <= i) C[pidx(i, j)] = cv[v] - acc[v >> 1][v & 1];
-        }
-    } else {
-        f4_t acc[2][2];
+        for (int r = 0; r < GR; ++r)
 #pragma unroll
-        for (int g = 0; g < 2; ++g)
+            for (int e = 0; e < NE; ++e)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) acc[g][h] = f4_t{0.f, 0.f, 0.f, 0.f};
-        for (int k0 = 0; k0 < NB; k0 += 4) {
-            const int kr = (k0 + (lane >> 4)) * UP;
-            float a[2], bb[2];
+                for (int c = 0; c < NC; ++c)
+                    cv[r][e][c] = in(q + r, e, c) ? buf_load<T>(rc, at(q + r, e) + 16u * c * (uint32_t)sizeof(T)) : T(0);
 #pragma unroll
-            for (int g = 0; g < 2; ++g) a[g] = Pi[kr + 32 * wr + 16 * g + (lane & 15)];
+        for (int r = 0; r < GR; ++r)
 #pragma unroll
-            for (int h = 0; h < 2; ++h) bb[h] = Y[kr + 32 * wc + 16 * h + (lane & 15)];
+            for (int e = 0; e < NE; ++e)
 #pragma unroll
-            for (int g = 0; g < 2; ++g)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) acc[g][h] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[g], bb[h], acc[g][h], 0, 0, 0);
-        }
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            const int64_t i = r0 + 32 * wr + 16 * (v >> 3) + 4 * (lane >> 4) + (v & 3);
-            const int64_t j = c0 + 32 * wc + 16 * ((v >> 2) & 1) + (lane & 15);
-            if (i < n && j <= i) C[pidx(i, j)] = cv[v] - acc[v >> 3][(v >> 2) & 1][v & 3];
-        }
+                for (int c = 0; c < NC; ++c)
+                    if (in(q + r, e, c))
+                        buf_store<T>(rc, at(q + r, e) + 16u * c * (uint32_t)sizeof(T), cv[r][e][c] - M::get(acc[q + r][c], e));
     }
 }
 
@@ -374,55 +740,62 @@ __global__ __launch_bounds__(256) void k_atb_sum(const double* __restrict__ part
     out[(e / nrhs) * ldo + e % nrhs] = (T)s;
 }
 
-// Right-looking factorization.  With a helper stream s2 and two events the
-// update of block k is split: its first tile column (what block k + 1 needs)
-// runs on s, the rest on s2, so the diagonal factor and row solve of block
-// k + 1 overlap the bulk of the update.  Ordering: the rest of update k waits
-// for the row solve and first column of k (event e); the first column of
-// update k + 1 waits for the rest of update k (event f), whose tiles it
-// overlaps; s joins s2 at the end.
+// The factorization on s with a helper stream s2 and two events.  Ordering:
+// the rest of the update after panel p waits for the panel (event e); the
+// next panel's part of the update after panel p + 1 waits for the rest of the
+// update after p (event f), whose tiles it overlaps; s joins s2 at the end.
+// Trailing matrices of at most kOneLaunch 64 x 64 tiles take one launch on s:
+// it lasts no longer than the next panel's part, and the events cost more
+// than the overlap brings.
+// ws: two 64 x 64 blocks.
+// Measured (FP64): a step alone takes 16 us with no panel columns to its left
+// and 6 us more for every 64 (its diagonal block alone took 67 us and the rows
+// below 51 us as launches of their own); the first update at n = 10000 takes
+// 477 us alone, 50 TFLOP/s.  Factor at n = 10000 25.9 -> 10.7 ms, of which the
+// updates are bound by the tiles and, from about 5000 columns on, the rest by
+// the chain of steps: n = 2048 3.4 -> 1.0 ms.
+constexpr int64_t kOneLaunch = 600;
+
 template <typename T>
-hipError_t potrf_t(T* C, int64_t n, int32_t* info, hipStream_t s, hipStream_t s2, hipEvent_t e, hipEvent_t f) {
+hipError_t potrf_t(T* C, int64_t n, int32_t* info, T* ws, hipStream_t s, hipStream_t s2, hipEvent_t e, hipEvent_t f) {
     bool rest_pending = false;
     hipError_t err;
-    for (int64_t kb = 0; kb < n; kb += NB) {
-        const int w = (int)(n - kb < NB ? n - kb : NB);
-        const int64_t rest = n - kb - w;
-        const int64_t nrb = (rest + NB - 1) / NB;
+    for (int64_t pb = 0; pb < n; pb += NP) {
+        const int64_t pe = n < pb + NP ? n : pb + NP;
         {
             ProfScope ps(ATA_KERNEL_FACTOR_PANEL, s);
-            hipLaunchKernelGGL(k_chol_diag<T>, dim3(1), dim3(256), 0, s, C, kb, w, info);
-            if ((err = hipGetLastError()) != hipSuccess) return err;
-        }
-        if (nrb == 0) continue;
-        {
-            ProfScope ps(ATA_KERNEL_FACTOR_PANEL, s);
-            hipLaunchKernelGGL(k_chol_rows<T>, dim3((unsigned)nrb), dim3(256), 0, s, C, n, kb, w);
-            if ((err = hipGetLastError()) != hipSuccess) return err;
-        }
-        if (!s2 || nrb == 1) {
-            if (rest_pending) {
-                if ((err = hipStreamWaitEvent(s, f, 0)) != hipSuccess) return err;
-                rest_pending = false;
+            for (int64_t kb = pb; kb < pe; kb += NB) {
+                const int w = (int)(n - kb < NB ? n - kb : NB);
+                const int64_t rest = n - kb - w, step = kb / NB;
+                hipLaunchKernelGGL(k_chol_panel<T>, dim3((unsigned)(rest > 0 ? (rest + NB - 1) / NB : 1)), dim3(256),
+                                   0, s, C, n, pb, kb, w, info, ws + (step & 1) * NB * NB,
+                                   kb > 0 ? ws + ((step - 1) & 1) * NB * NB : (const T*)nullptr);
+                if ((err = hipGetLastError()) != hipSuccess) return err;
             }
+        }
+        if (pe >= n) break;
+        if (rest_pending && (err = hipStreamWaitEvent(s, f, 0)) != hipSuccess) return err;
+        rest_pending = false;
+        const int64_t t64 = (n - pe + 63) / 64, all = t64 * (t64 + 1) / 2;
+        if (all <= kOneLaunch) {
             ProfScope ps(ATA_KERNEL_FACTOR_UPDATE, s);
-            hipLaunchKernelGGL(k_chol_update<T>, dim3((unsigned)(nrb * (nrb + 1) / 2)), dim3(256), 0, s, C, n, kb,
-                               w, (int)nrb, 0);
+            hipLaunchKernelGGL((k_chol_syrk<T, 64>), dim3((unsigned)all), dim3(256), 0, s, C, n, pb, 0);
             if ((err = hipGetLastError()) != hipSuccess) return err;
             continue;
-        }
-        if (rest_pending && (err = hipStreamWaitEvent(s, f, 0)) != hipSuccess) return err;
-        {
-            ProfScope ps(ATA_KERNEL_FACTOR_UPDATE, s);
-            hipLaunchKernelGGL(k_chol_update<T>, dim3((unsigned)nrb), dim3(256), 0, s, C, n, kb, w, (int)nrb, 1);
-            if ((err = hipGetLastError()) != hipSuccess) return err;
         }
         if ((err = hipEventRecord(e, s)) != hipSuccess) return err;
         if ((err = hipStreamWaitEvent(s2, e, 0)) != hipSuccess) return err;
         {
+            constexpr int64_t np = NP / 64;
+            ProfScope ps(ATA_KERNEL_FACTOR_UPDATE, s);
+            hipLaunchKernelGGL((k_chol_syrk<T, 64>), dim3((unsigned)(np * (np + 1) / 2 + (t64 - np) * np)), dim3(256),
+                               0, s, C, n, pb, 1);
+            if ((err = hipGetLastError()) != hipSuccess) return err;
+        }
+        {
+            const int64_t t = (n - pe + 127) / 128 - NP / 128;  // tile rows beyond the next panel
             ProfScope ps(ATA_KERNEL_FACTOR_UPDATE, s2);
-            hipLaunchKernelGGL(k_chol_update<T>, dim3((unsigned)((nrb - 1) * nrb / 2)), dim3(256), 0, s2, C, n, kb,
-                               w, (int)nrb, 2);
+            hipLaunchKernelGGL((k_chol_syrk<T, 128>), dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, s2, C, n, pb, 2);
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
         if ((err = hipEventRecord(f, s2)) != hipSuccess) return err;
@@ -498,9 +871,12 @@ hipError_t launch_transpose(int elem_bytes, const void* A, int64_t m, int64_t n,
     return hipGetLastError();
 }
 
-hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, hipStream_t s, hipStream_t s2, hipEvent_t e,
-                        hipEvent_t f) {
-    return f32 ? potrf_t((float*)C, n, info, s, s2, e, f) : potrf_t((double*)C, n, info, s, s2, e, f);
+size_t potrf_ws_bytes() { return 2 * NB * NB * sizeof(double); }
+
+hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, void* ws, hipStream_t s, hipStream_t s2,
+                        hipEvent_t e, hipEvent_t f) {
+    return f32 ? potrf_t((float*)C, n, info, (float*)ws, s, s2, e, f)
+               : potrf_t((double*)C, n, info, (double*)ws, s, s2, e, f);
 }
 
 int64_t atb_chunks(int64_t m, int64_t n) {

@@ -56,8 +56,12 @@ int potrf_checked(void* C, int64_t n, int dtype, int32_t* info, hipStream_t s) {
         SOLVE_TRY(hipEventCreateWithFlags(&nl.f, hipEventDisableTiming));
         la = nl;
     }
-    SOLVE_TRY(launch_potrf(dtype == ATA_F32, C, n, info, s, la.s2, la.e, la.f));
-    return ATA_OK;
+    void* ws = nullptr;
+    SOLVE_TRY(hipMallocAsync(&ws, potrf_ws_bytes(), s));
+    hipError_t e = launch_potrf(dtype == ATA_F32, C, n, info, ws, s, la.s2, la.e, la.f);
+    const hipError_t e2 = hipFreeAsync(ws, s);
+    if (e == hipSuccess) e = e2;
+    return e == hipSuccess ? ATA_OK : hip_fail(e);
 }
 
 int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs, int64_t ldb, void* out,
