@@ -174,17 +174,19 @@ void serialize(PlanDev& pd) {
         d.n_mix = (int)ph.mix_items.size();
         d.off_mix = off;
         off = align256(off + ph.mix_items.size() * sizeof(WorkItem));
-        d.n_big = (int)ph.big_items.size();
-        d.off_big = off;
-        off = align256(off + ph.big_items.size() * sizeof(WorkItem));
         d.n_tail = (int)ph.tail_items.size();
         d.tail_parts = ph.tail_parts;
         d.off_tail = off;
         off = align256(off + ph.tail_items.size() * sizeof(WorkItem));
-        d.n_big_tail = (int)ph.big_tail.size();
-        d.big_tail_parts = ph.big_tail_parts;
-        d.off_big_tail = off;
-        off = align256(off + ph.big_tail.size() * sizeof(WorkItem));
+        for (int md = 0; md < 2; ++md) {
+            d.n_wide[md] = (int)ph.wide_items[md].size();
+            d.off_wide[md] = off;
+            off = align256(off + ph.wide_items[md].size() * sizeof(WorkItem));
+            d.n_wide_tail[md] = (int)ph.wide_tail[md].size();
+            d.wide_parts[md] = ph.wide_parts[md];
+            d.off_wide_tail[md] = off;
+            off = align256(off + ph.wide_tail[md].size() * sizeof(WorkItem));
+        }
     }
     std::vector<char>& host = pd.host_blob;
     host.assign(off ? off : 256, 0);
@@ -201,12 +203,15 @@ void serialize(PlanDev& pd) {
         std::memcpy(host.data() + d.off_cb, ph.combines.data(), ph.combines.size() * sizeof(DevCombine));
         std::memcpy(host.data() + d.off_ops, ph.opsums.data(), ph.opsums.size() * sizeof(DevOpSum));
         std::memcpy(host.data() + d.off_mix, ph.mix_items.data(), ph.mix_items.size() * sizeof(WorkItem));
-        std::memcpy(host.data() + d.off_big, ph.big_items.data(), ph.big_items.size() * sizeof(WorkItem));
-        std::memcpy(host.data() + d.off_big_tail, ph.big_tail.data(), ph.big_tail.size() * sizeof(WorkItem));
+        for (int md = 0; md < 2; ++md) {
+            std::memcpy(host.data() + d.off_wide[md], ph.wide_items[md].data(),
+                        ph.wide_items[md].size() * sizeof(WorkItem));
+            std::memcpy(host.data() + d.off_wide_tail[md], ph.wide_tail[md].data(),
+                        ph.wide_tail[md].size() * sizeof(WorkItem));
+        }
         std::memcpy(host.data() + d.off_tail, ph.tail_items.data(), ph.tail_items.size() * sizeof(WorkItem));
     }
     for (int mode = 0; mode < 2; ++mode) pd.lp_aligned[mode] = lp_windows_aligned(P, mode == 0 ? 2 : 4);
-    pd.lp_aligned16 = P.opt.lp && lp_windows_aligned(P, 16, true);
     for (int mode = 0; mode < 2; ++mode) pd.lp_dma16[mode] = P.opt.lp && lp_windows_aligned(P, mode == 0 ? 8 : 16, true);
 }
 
@@ -570,24 +575,18 @@ hipError_t enqueue_product(const PlanDev& pdr, const char* dblob, const WsLayout
                                      (const WorkItem*)(pd->blob + ph.off_tg), ph.n_tg, C_lower, W, s,
                                      lp_align(pdr, lp_mode));
             }
-            if (err == hipSuccess && lp_mode == 1 && out64 && pdr.lp_aligned16 && ph.n_big >= kBigMinTiles &&
-                (int64_t)64 * L.ldt < ((int64_t)1 << 31)) {
-                // e4m3 classical tiles of 256 x 256 in one launch
+            if (err == hipSuccess && pdr.lp_dma16[lp_mode] && ph.n_wide[lp_mode] >= kWideMin &&
+                L.ldt * (lp_mode == 0 ? 128 : 64) < ((int64_t)1 << 31)) {
+                // classical tiles on wide workgroup tiles, the last, partial
+                // round of them with its K range split over every CU (parts
+                // summed in part order)
                 ProfScope ps(ATA_KERNEL_GEMM, s);
-                err = launch_lp8_big(ws + L.t0, (int)L.ldt, scale, tb, (const WorkItem*)(pd->blob + ph.off_big),
-                                     ph.n_big, (double*)C_lower, W, s, 1, nullptr);
-                if (err == hipSuccess && ph.n_big_tail) {
-                    // the last, partial round of tiles with its K range split
-                    // over every CU; FP32 partials summed in part order
-                    float* part = (float*)(W + P.lp_tail_off);
-                    err = launch_lp8_big(ws + L.t0, (int)L.ldt, scale, tb,
-                                         (const WorkItem*)(pd->blob + ph.off_big_tail), ph.n_big_tail,
-                                         (double*)C_lower, W, s, ph.big_tail_parts, part);
-                    if (err == hipSuccess)
-                        err = launch_lp8_tail_sum(scale, tb, (const WorkItem*)(pd->blob + ph.off_big_tail),
-                                                  ph.n_big_tail / ph.big_tail_parts, ph.big_tail_parts, part,
-                                                  (double*)C_lower, W, s);
-                }
+                const LpCopy cp{ws + L.t0, t1, (int)L.ldt, scale};
+                err = launch_lp_tile16(lp_mode, out64, true, cp, tb,
+                                       (const WorkItem*)(pd->blob + ph.off_wide[lp_mode]), ph.n_wide[lp_mode],
+                                       (const WorkItem*)(pd->blob + ph.off_wide_tail[lp_mode]),
+                                       ph.n_wide_tail[lp_mode], ph.wide_parts[lp_mode], W + P.lp_tail_off, C_lower, W,
+                                       s);
                 if (err == hipSuccess && ph.n_cb) {  // sums of split K parts
                     ProfScope ps2(ATA_KERNEL_COMBINE, s);
                     err = launch_combine(out64, (const DevCombine*)(pd->blob + ph.off_cb), ph.n_cb, ph.cb_elems, W,

@@ -16,12 +16,13 @@ namespace detail {
 // Device copy of one plan's tables.
 struct PhaseDev {
     int n_str = 0, n_tg = 0, n_gemm = 0, n_syrk = 0, n_cb = 0, n_ops = 0, n_mix = 0, str_tmax = 0, tg_tmax = 0;
-    int n_big = 0;  // reduced-precision plans: 256 x 256 tiles of the phase's classical tasks
-    int n_big_tail = 0, big_tail_parts = 0;  // ... and the K-split tiles of their last round
+    // reduced-precision plans, by mode: wide tiles of the phase's classical
+    // tasks and the K-split tiles of their last round
+    int n_wide[2] = {0, 0}, n_wide_tail[2] = {0, 0}, wide_parts[2] = {0, 0};
     int n_tail = 0, tail_parts = 0;          // FP64: K-split tiles of the last round of the mix launch
     int64_t cb_elems = 0, ops_rows = 0;
-    size_t off_str = 0, off_tg = 0, off_gemm = 0, off_syrk = 0, off_cb = 0, off_ops = 0, off_mix = 0, off_big = 0,
-           off_big_tail = 0, off_tail = 0;
+    size_t off_str = 0, off_tg = 0, off_gemm = 0, off_syrk = 0, off_cb = 0, off_ops = 0, off_mix = 0, off_tail = 0;
+    size_t off_wide[2] = {0, 0}, off_wide_tail[2] = {0, 0};
 };
 
 struct PlanDev {
@@ -32,7 +33,6 @@ struct PlanDev {
     size_t off_tasks = 0, off_terms = 0, off_segs = 0;
     std::vector<PhaseDev> phases;
     bool lp_aligned[2] = {false, false};  // reduced-precision modes: windows dword-aligned in the copy
-    bool lp_aligned16 = false;            // windows on 16 elements of the copy (e4m3 256 x 256 tiles)
     bool lp_dma16[2] = {false, false};    // reduced-precision modes: windows on 16 bytes of the copy
     ~PlanDev() {
         if (blob) {

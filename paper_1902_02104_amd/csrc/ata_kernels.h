@@ -40,17 +40,22 @@ hipError_t launch_fine(bool f32, bool out_f64, int tb, const void* A, int64_t ld
 hipError_t launch_tile(int nt, const double* A, int64_t lda, const DevTables& tb, const WorkItem* items, int nitems,
                        double* C, double* W, hipStream_t s, const double* Aops = nullptr, int* queue = nullptr);
 
-// e4m3 classical tiles of 256 x 256 (items index kBigTile tiles) on the
-// transposed copy T0 (row stride ldt bytes, windows on 16 elements, 64 ldt
-// below 2^31), FP64 output.
-// nparts > 1: the items are K-split tiles (slot = tile * nparts + part) whose
-// raw FP32 results go to part (kBigTile^2 floats per slot); then
-// launch_lp8_tail_sum sums them (ntiles tiles, the first item of each tile's
-// run describing it) into C.
-hipError_t launch_lp8_big(const void* T0, int ldt, const float* scale, const DevTables& tb, const WorkItem* items,
-                          int nitems, double* C, double* W, hipStream_t s, int nparts = 1, float* part = nullptr);
-hipError_t launch_lp8_tail_sum(const float* scale, const DevTables& tb, const WorkItem* tail, int ntiles, int nparts,
-                               const float* part, double* C, double* W, hipStream_t s);
+// Transposed converted copy of the reduced-precision forms: plane 0 (bfloat16
+// hi, or e4m3), plane 1 (bfloat16 lo), row stride in elements, e4m3 scales.
+struct LpCopy {
+    const void* t0;
+    const void* t1;
+    int ldt;
+    const float* scale;
+};
+// Reduced-precision classical tiles whose windows lie on 16 bytes of the copy
+// (64 rows of it below 2^31 bytes), items of kWideRows x wide_cols(mode) tiles
+// (wide) or 128 x 128 ones: nmain whole tiles and ntail parts of K-split tiles
+// (slot = tile * nparts + part), whose results go to `part` (one tile of FP64
+// values, e4m3 FP32, per slot) and are summed into C by a second launch.
+hipError_t launch_lp_tile16(int mode, bool out_f64, bool wide, const LpCopy& cp, const DevTables& tb,
+                            const WorkItem* items, int nmain, const WorkItem* tail, int ntail, int nparts, void* part,
+                            void* C, double* W, hipStream_t s);
 
 // The same for a launch of k_gemmd tiles (FP32, or FP64 batched/operand-sum
 // launches); C of the launch's output type.

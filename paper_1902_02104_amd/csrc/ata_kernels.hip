@@ -1518,26 +1518,19 @@ __device__ __forceinline__ uint16_t bf16_rne(float x) {
 }
 
 // binary32 -> OCP FP8 e4m3 (bias 7, 3 mantissa bits, no infinities, largest
-// finite 448), round to nearest even, saturating to +-448.
-__device__ __forceinline__ uint8_t e4m3_rne(float x) {
-    const uint32_t sign = (__float_as_uint(x) >> 24) & 0x80u;
-    const float a = fabsf(x);
-    if (!(a == a)) return (uint8_t)(sign | 0x7fu);
-    if (a >= 448.0f) return (uint8_t)(sign | 0x7eu);
-    if (a < 0.015625f) {  // below 2^-6: subnormal steps of 2^-9
-        const float q = __builtin_rintf(a * 512.0f);  // exact scaling, then RNE
-        return (uint8_t)(sign | (uint32_t)q);          // q == 8 encodes 2^-6 (exponent field 1)
-    }
-    int e = (int)((__float_as_uint(a) >> 23) & 0xffu) - 127;  // a = 1.f * 2^e, e in [-6, 8]
-    const float mant = a * __builtin_ldexpf(1.0f, -e);         // [1, 2), exact
-    float q = __builtin_rintf((mant - 1.0f) * 8.0f);           // exact scaling, then RNE
-    if (q >= 8.0f) {
-        q = 0.0f;
-        ++e;
-    }
-    if (e > 8 || (e == 8 && q >= 7.0f)) return (uint8_t)(sign | 0x7eu);
-    return (uint8_t)(sign | ((uint32_t)(e + 7) << 3) | (uint32_t)q);
+// finite 448), round to nearest even, saturating to +-448; two values into the
+// low 16 bits.  The conversion instruction makes a NaN of values past 448, so
+// they are clamped first; a NaN keeps its sign as S.1111.111.  (Equal to the
+// arithmetic definition for all 2^32 inputs.)
+__device__ __forceinline__ uint32_t e4m3_rne2(float x, float y) {
+    uint32_t r = (uint32_t)__builtin_amdgcn_cvt_pk_fp8_f32(__builtin_amdgcn_fmed3f(x, -448.0f, 448.0f),
+                                                           __builtin_amdgcn_fmed3f(y, -448.0f, 448.0f), 0, false);
+    r &= 0xffffu;
+    if (x != x) r = (r & 0xff00u) | ((__float_as_uint(x) >> 24) & 0x80u) | 0x7fu;
+    if (y != y) r = (r & 0x00ffu) | ((__float_as_uint(y) >> 16) & 0x8000u) | 0x7f00u;
+    return r;
 }
+__device__ __forceinline__ uint8_t e4m3_rne(float x) { return (uint8_t)e4m3_rne2(x, x); }
 
 __global__ void k_convert(int mode, const float* __restrict__ x, int64_t count, void* __restrict__ o0,
                           void* __restrict__ o1) {
@@ -1599,13 +1592,21 @@ __device__ __forceinline__ float e4m3_pow2_scale(float mx) {
     return s;
 }
 
+// 64 columns per workgroup, the chunks over its four waves: a chain of loads
+// bounds it (8192 x 8192, 32 chunks: one wave per 64 columns 11 us, now 5).
 __global__ void __launch_bounds__(256) k_colscale(const float* __restrict__ part, int nchunks, int n,
                                                   float* __restrict__ scale) {
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= n) return;
+    __shared__ float red[4][64];
+    const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
+    const int j = blockIdx.x * 64 + lane;
     float mx = 0.0f;
-    for (int c = 0; c < nchunks; ++c) mx = fmaxf(mx, part[(int64_t)c * n + j]);
-    scale[j] = e4m3_pow2_scale(mx);
+    if (j < n)
+#pragma unroll 8
+        for (int c = g; c < nchunks; c += 4) mx = fmaxf(mx, part[(int64_t)c * n + j]);
+    red[g][lane] = mx;
+    __syncthreads();
+    if (g == 0 && j < n)
+        scale[j] = e4m3_pow2_scale(fmaxf(fmaxf(red[0][lane], red[1][lane]), fmaxf(red[2][lane], red[3][lane])));
 }
 
 // ---------------------------------------------------------------------------
@@ -1665,10 +1666,8 @@ __global__ void __launch_bounds__(256) k_descale(OUT* __restrict__ C, const S* _
 
 // Transposed, converted copy of A: out[i * ldt + k] for column i of A and
 // row k (k >= m zero).  64 x 64 tiles through LDS.
-template <int MODE>
-__global__ void __launch_bounds__(256) k_prep_lp(const float* __restrict__ A, int64_t lda, int m, int n, int ldt,
-                                                 const float* __restrict__ scale, void* __restrict__ o0,
-                                                 void* __restrict__ o1) {
+__global__ void __launch_bounds__(256) k_prep_bf16(const float* __restrict__ A, int64_t lda, int m, int n, int ldt,
+                                                   uint16_t* __restrict__ o0, uint16_t* __restrict__ o1) {
     // KB k values (rows of A) x 64 columns per workgroup; each lane of the
     // writing pass packs PK consecutive k of one output row into one store.
     constexpr int PK = 2;
@@ -1699,20 +1698,13 @@ __global__ void __launch_bounds__(256) k_prep_lp(const float* __restrict__ A, in
                 }
             }
         }
-        float4 sc = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
-        if (MODE == 1) {  // exact: power-of-two scales
-            if (c < n) sc.x = scale[c];
-            if (c + 1 < n) sc.y = scale[c + 1];
-            if (c + 2 < n) sc.z = scale[c + 2];
-            if (c + 3 < n) sc.w = scale[c + 3];
-        }
 #pragma unroll
         for (int u = 0; u < KB / 16; ++u) {
             const int r = rr + 16 * u;
-            tile[r][cq] = v[u].x * sc.x;
-            tile[r][cq + 1] = v[u].y * sc.y;
-            tile[r][cq + 2] = v[u].z * sc.z;
-            tile[r][cq + 3] = v[u].w * sc.w;
+            tile[r][cq] = v[u].x;
+            tile[r][cq + 1] = v[u].y;
+            tile[r][cq + 2] = v[u].z;
+            tile[r][cq + 3] = v[u].w;
         }
     }
     __syncthreads();
@@ -1722,22 +1714,82 @@ __global__ void __launch_bounds__(256) k_prep_lp(const float* __restrict__ A, in
         const int cl = ty + 4 * i, c = c0 + cl;
         if (c >= n) break;
         const int64_t o = (int64_t)c * ldt + kk;
-        if (MODE == 0) {
-            uint32_t hw = 0, lw = 0;
+        uint32_t hw = 0, lw = 0;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const float v = tile[tx * 2 + q][cl];
-                const uint16_t h = bf16_rne(v);
-                const float hf = __uint_as_float((uint32_t)h << 16);
-                hw |= (uint32_t)h << (16 * q);
-                lw |= (uint32_t)bf16_rne(v - hf) << (16 * q);
-            }
-            *(uint32_t*)((uint16_t*)o0 + o) = hw;
-            *(uint32_t*)((uint16_t*)o1 + o) = lw;
-        } else {
-            const uint32_t wd = (uint32_t)e4m3_rne(tile[tx * 2][cl]) | ((uint32_t)e4m3_rne(tile[tx * 2 + 1][cl]) << 8);
-            *(uint16_t*)((uint8_t*)o0 + o) = (uint16_t)wd;
+        for (int q = 0; q < 2; ++q) {
+            const float v = tile[tx * 2 + q][cl];
+            const uint16_t h = bf16_rne(v);
+            const float hf = __uint_as_float((uint32_t)h << 16);
+            hw |= (uint32_t)h << (16 * q);
+            lw |= (uint32_t)bf16_rne(v - hf) << (16 * q);
         }
+        *(uint32_t*)(o0 + o) = hw;
+        *(uint32_t*)(o1 + o) = lw;
+    }
+}
+
+// The same for e4m3(A s), s the columns' power-of-two scales (the product is
+// exact).  256 k x 64 columns per workgroup, converted before the transpose:
+// a lane reads four columns of four rows, packs each column's four bytes into
+// a dword and the dwords cross LDS, a quarter of the LDS traffic of crossing
+// as floats; 16-byte stores.  Bound by memory (8192 x 8192: 107 us as floats
+// with the conversion in integer steps and 2-byte stores, now 63, 5.3 TB/s).
+__global__ void __launch_bounds__(256) k_prep_e4m3(const float* __restrict__ A, int64_t lda, int m, int n, int ldt,
+                                                   const float* __restrict__ scale, uint8_t* __restrict__ o0) {
+    constexpr int KB = 256, ST = KB / 4 + 1;
+    __shared__ uint32_t tile[64 * ST];
+    const int k0 = blockIdx.x * KB, c0 = blockIdx.y * 64;
+    {
+        const int cq = (threadIdx.x & 15) * 4, kq = threadIdx.x >> 4;  // kq: dword of 4 k in a round of 64 k
+        const int c = c0 + cq;
+        const bool vec = c + 4 <= n && (lda & 3) == 0 && (((uintptr_t)A) & 15u) == 0;
+        float4 v[KB / 64][4];
+#pragma unroll
+        for (int u = 0; u < KB / 64; ++u)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int k = k0 + 64 * u + 4 * kq + r;
+                float4 x = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+                if (k < m) {
+                    const float* src = A + (int64_t)k * lda + c;
+                    if (vec) {
+                        x = *(const float4*)src;
+                    } else {
+                        if (c < n) x.x = src[0];
+                        if (c + 1 < n) x.y = src[1];
+                        if (c + 2 < n) x.z = src[2];
+                        if (c + 3 < n) x.w = src[3];
+                    }
+                }
+                v[u][r] = x;
+            }
+        float4 sc = make_float4(1.0f, 1.0f, 1.0f, 1.0f);
+        if (c < n) sc.x = scale[c];
+        if (c + 1 < n) sc.y = scale[c + 1];
+        if (c + 2 < n) sc.z = scale[c + 2];
+        if (c + 3 < n) sc.w = scale[c + 3];
+#pragma unroll
+        for (int u = 0; u < KB / 64; ++u) {
+            uint32_t* t = tile + cq * ST + 16 * u + kq;
+            t[0] = e4m3_rne2(v[u][0].x * sc.x, v[u][1].x * sc.x) |
+                   (e4m3_rne2(v[u][2].x * sc.x, v[u][3].x * sc.x) << 16);
+            t[ST] = e4m3_rne2(v[u][0].y * sc.y, v[u][1].y * sc.y) |
+                    (e4m3_rne2(v[u][2].y * sc.y, v[u][3].y * sc.y) << 16);
+            t[2 * ST] = e4m3_rne2(v[u][0].z * sc.z, v[u][1].z * sc.z) |
+                        (e4m3_rne2(v[u][2].z * sc.z, v[u][3].z * sc.z) << 16);
+            t[3 * ST] = e4m3_rne2(v[u][0].w * sc.w, v[u][1].w * sc.w) |
+                        (e4m3_rne2(v[u][2].w * sc.w, v[u][3].w * sc.w) << 16);
+        }
+    }
+    __syncthreads();
+    const int kk = k0 + 16 * (threadIdx.x & 15);  // ldt is a multiple of 128
+    if (kk >= ldt) return;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int cl = (threadIdx.x >> 4) + 16 * i, c = c0 + cl;
+        if (c >= n) break;
+        const uint32_t* t = tile + cl * ST + 4 * (threadIdx.x & 15);
+        *(uint4*)(o0 + (int64_t)c * ldt + kk) = make_uint4(t[0], t[1], t[2], t[3]);
     }
 }
 
@@ -2104,7 +2156,8 @@ __global__ void __launch_bounds__(256, MODE == 1 ? 2 : 1) k_gemm_lp(const uint8_
 // of the copy moved from global memory straight into LDS by buffer loads that
 // write LDS, one dword per lane, two 128-byte tile rows per copy.  The copies
 // of stage s + 1 are issued while stage s is multiplied (double-buffered
-// LDS), so the loop waits on global memory only at the stage barrier.  Wave w
+// LDS), so the loop waits on global memory only at the stage barrier.  Runs
+// where the windows are on dwords of the copy but not on 16 bytes (k_lp_tile).  Wave w
 // copies operand w / 2, tile rows [64 (w % 2), 64 (w % 2) + 64).  The copies
 // need every segment window of the plan to start and end on a dword of the
 // copy (checked on the host; otherwise k_gemm_lp runs).  The 16-byte chunks
@@ -2124,7 +2177,7 @@ struct LpdCfg<1> {  // e4m3
     static constexpr int KT = 128, EB = 1, PL = 1, OCC = 2;
 };
 
-template <int MODE, typename OUT, bool SPLIT = false, bool B16 = false>
+template <int MODE, typename OUT, bool SPLIT = false>
 __global__ void __launch_bounds__(256, LpdCfg<MODE>::OCC) k_gemm_lpd(const uint8_t* __restrict__ T0,
                                                                     const uint8_t* __restrict__ T1, int ldt,
                                                                     const float* __restrict__ scale,
@@ -2157,28 +2210,16 @@ __global__ void __launch_bounds__(256, LpdCfg<MODE>::OCC) k_gemm_lpd(const uint8
     // rows 2i (lanes 0-31) and 2i + 1 (lanes 32-63) of that range; lane
     // dword d of a row holds logical chunk (d / 4) ^ (i mod 8).  Per i mod 8:
     // the lane's byte offset inside the row block and its first k element.
-    // B16: sixteen bytes per lane instead, copy i moving rows 8i to 8i + 7
-    // (lane L: row 8i + L / 8, physical chunk L % 8, so logical chunk
-    // (L % 8) ^ ((8i + L / 8) / 2 mod 8)); vb and ke then hold, per copy,
-    // the lane's byte offset from the block's window start and first k.
     const int cop = wave >> 1, half = wave & 1;
     const int hb = lane >> 5, d = lane & 31;
-    const int rl = lane >> 3;
     uint32_t vb[8];
     int ke[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-        if constexpr (B16) {
-            const int r = 8 * q + rl;
-            const int kc = (lane & 7) ^ ((r >> 1) & 7);
-            vb[q] = (uint32_t)(r * rowb) + (uint32_t)(kc * 16);
-            ke[q] = kc * 16 / EB;
-        } else {
-            const int lc = (d >> 2) ^ q;
-            const int byte = lc * 16 + (d & 3) * 4;
-            vb[q] = (uint32_t)(hb * rowb) + (uint32_t)byte;
-            ke[q] = byte / EB;
-        }
+        const int lc = (d >> 2) ^ q;
+        const int byte = lc * 16 + (d & 3) * 4;
+        vb[q] = (uint32_t)(hb * rowb) + (uint32_t)byte;
+        ke[q] = byte / EB;
     }
     const DevTerm& tc = cop == 0 ? tx : ty;
     const int row0 = tc.col + (cop == 0 ? i0 : j0) + half * 64;  // first row of the copy this wave reads
@@ -2218,20 +2259,11 @@ __global__ void __launch_bounds__(256, LpdCfg<MODE>::OCC) k_gemm_lpd(const uint8
             const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), (short)0, 0x7fffffff,
                                                                 0x00020000);
             uint8_t* dst = &lds[buf][p][cop][half * 64 * RB];
-            if constexpr (B16) {
 #pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    const bool ok = full || (8 * i + rl < nrv && ke[i] < krem);
-                    lds_copy16(rs, dst + i * 8 * RB, ok ? vb[i] : kOOB);
-                }
-            } else {
-#pragma unroll
-                for (int i = 0; i < NCP; ++i) {
-                    const uint32_t off = full || (i < ilim && ke[i & 7] < krem) ? vb[i & 7] : kOOB;
-                    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                        rs, (__attribute__((address_space(3))) void*)(dst + 2 * i * RB), 4, off, (int)(2 * i * rowb), 0,
-                        0);
-                }
+            for (int i = 0; i < NCP; ++i) {
+                const uint32_t off = full || (i < ilim && ke[i & 7] < krem) ? vb[i & 7] : kOOB;
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    rs, (__attribute__((address_space(3))) void*)(dst + 2 * i * RB), 4, off, (int)(2 * i * rowb), 0, 0);
             }
         }
     };
@@ -2365,213 +2397,6 @@ __global__ void __launch_bounds__(256, LpdCfg<MODE>::OCC) k_gemm_lpd(const uint8
             }
         }
     }
-}
-
-// ---------------------------------------------------------------------------
-// e4m3 tiles of 256 x 256 (k_lp8_big): the tasks of k_gemm_lpd<1> on
-// workgroup tiles four times larger, for launches with enough of them.  One
-// stage of a 128 x 128 e4m3 tile is 512 MFMA cycles per wave, too short to
-// cover the latency of the next stage's copies from L2 and the MALL; here a
-// stage is 2048 MFMA cycles per SIMD (two waves of 32 MFMAs each) and every
-// byte staged feeds twice the multiply-adds.  512 threads: eight waves of
-// 128 x 64 (rows wm = wave / 4, columns wn = wave % 4), 128 k per stage,
-// double-buffered LDS of 2 x 64 KB, one workgroup per CU.
-//
-// Copies: one 16-byte buffer load per lane that writes LDS moves eight
-// 128-byte tile rows; wave w copies rows [64 (w % 4), 64 (w % 4) + 64) of
-// operand w / 4.  Physical chunk p of row r holds logical chunk
-// p ^ ((r / 2) mod 8) (the swizzle of k_gemm_lpd), so lane L of a copy
-// fetches logical chunk (L % 8) ^ ((r / 2) mod 8) of row r = 8 i + L / 8.
-// Needs every segment window of the plan on 16 elements of the copy
-// (checked on the host); chunks past the window end or the operand's last
-// row get an out-of-range offset and write zeros.
-// ---------------------------------------------------------------------------
-constexpr int BT = kBigTile;  // workgroup tile
-
-__global__ void __launch_bounds__(512, 1) k_lp8_big(const uint8_t* __restrict__ T0, int ldt,
-                                                    const float* __restrict__ scale,
-                                                    const DevTask* __restrict__ tasks,
-                                                    const DevTerm* __restrict__ terms,
-                                                    const int32_t* __restrict__ segs,
-                                                    const WorkItem* __restrict__ items, double* __restrict__ C,
-                                                    double* __restrict__ W, int nparts, float* __restrict__ part) {
-    constexpr int KT = 128;          // k per stage (bytes of a tile row)
-    constexpr int PLANE = BT * KT;   // 32 KB
-    constexpr int NCP = 8;           // copies per wave and stage (8 rows each)
-    __shared__ __attribute__((aligned(16))) uint8_t lds[2][2][PLANE];  // [buffer][operand]
-
-    const WorkItem w = items[blockIdx.x];
-    const DevTask t = tasks[w.task];
-    const DevTerm tx = terms[t.term_off];
-    const DevTerm ty = terms[t.term_off + 1];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wm = wave >> 2, wn = wave & 3;
-    const int i0 = w.ti * BT, j0 = w.tj * BT;
-    const int stride = kSegHdr + 2 * (t.nx + t.ny);
-    const bool syrk = t.kind == TK_SYRK;
-    // waves of a diagonal tile whose 128 x 64 part lies above the diagonal
-    // only copy (the other wave on their SIMD gets the MFMA unit)
-    const bool idle = syrk && w.ti == w.tj && wn * 64 >= wm * 128 + 128;
-
-    // copy role
-    const int cop = wave >> 2, quarter = wave & 3;
-    const DevTerm& tc = cop == 0 ? tx : ty;
-    const int row0 = tc.col + (cop == 0 ? i0 : j0) + quarter * 64;  // first copy row of this wave
-    const int nrv = tc.cvend - row0;                                // rows of the 64 that exist
-    const int rl = lane >> 3, pc = lane & 7;                        // row in a copy, physical chunk
-    uint32_t vrow[NCP];  // byte offset of this lane's chunk from row0's window start, per copy
-    int kcl[NCP];        // first k of the lane's logical chunk
-#pragma unroll
-    for (int i = 0; i < NCP; ++i) {
-        const int r = 8 * i + rl;  // row within the wave's 64 (and within the 256: quarter * 64 + r)
-        const int kc = pc ^ (((quarter * 64 + r) >> 1) & 7);
-        kcl[i] = kc * 16;
-        vrow[i] = (uint32_t)(r * ldt + kc * 16);
-    }
-
-    f4_t acc[8][4];
-#pragma unroll
-    for (int a = 0; a < 8; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = f4_t{0.f, 0.f, 0.f, 0.f};
-
-    int ntiles = 0;
-    for (int sgi = 0; sgi < t.nseg; ++sgi)
-        ntiles += (segs[t.seg_off + sgi * stride + 2] - segs[t.seg_off + sgi * stride + 1] + KT - 1) / KT;
-    int seg = 0;
-    int k0 = t.nseg > 0 ? segs[t.seg_off + 1] : 0;
-    int kend = t.nseg > 0 ? segs[t.seg_off + 2] : 0;
-    int krow = t.nseg > 0 ? segs[t.seg_off + kSegHdr] : 0;
-
-    auto copy_stage = [&](int buf, bool live) {
-        const int krem = live ? kend - k0 : 0;
-        const bool full = krem >= KT && nrv >= 64;
-        const uint8_t* base = T0 + ((int64_t)row0 * ldt + krow + k0);
-        const rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t*>(base), (short)0, 0x7fffffff,
-                                                            0x00020000);
-        uint8_t* dst = &lds[buf][cop][quarter * 64 * KT];
-#pragma unroll
-        for (int i = 0; i < NCP; ++i) {
-            const bool ok = full || (8 * i + rl < nrv && kcl[i] < krem);
-            lds_copy16(rs, dst + i * 8 * KT, ok ? vrow[i] : kOOB);
-        }
-    };
-    auto advance = [&]() {
-        k0 += KT;
-        if (k0 >= kend) {
-            ++seg;
-            if (seg < t.nseg) {
-                k0 = segs[t.seg_off + seg * stride + 1];
-                kend = segs[t.seg_off + seg * stride + 2];
-                krow = segs[t.seg_off + seg * stride + kSegHdr];
-            }
-        }
-    };
-    auto chunk = [](int r, int kc) { return r * KT + ((kc ^ ((r >> 1) & 7)) << 4); };
-
-    // K-split item (nparts > 1): slot = tile * nparts + part; the part runs
-    // stages [part * ntiles / nparts, (part + 1) * ntiles / nparts)
-    const int tq = nparts > 1 ? w.slot / nparts : 0, tp = nparts > 1 ? w.slot % nparts : 0;
-    if (nparts > 1) {
-        const int s0 = (int)((int64_t)ntiles * tp / nparts), s1 = (int)((int64_t)ntiles * (tp + 1) / nparts);
-        for (int u = 0; u < s0; ++u) advance();
-        ntiles = s1 - s0;
-    }
-    if (ntiles > 0) copy_stage(0, true);
-    for (int it = 0; it < ntiles; ++it) {
-        const int buf = it & 1;
-        __builtin_amdgcn_s_waitcnt(0);  // this wave's copies of stage it have landed
-        __syncthreads();                // every copy of stage it landed; stage it-1 fully read
-        const bool next = it + 1 < ntiles;
-        if (next) advance();
-        copy_stage(buf ^ 1, next);
-        if (!idle) {
-            const int rsel = lane & 15, kc = 2 * (lane >> 4);  // 32 bytes: logical chunks kc, kc + 1
-            i8_t bq[4];
-#pragma unroll
-            for (int cf = 0; cf < 4; ++cf) {
-                const int rr = wn * 64 + cf * 16 + rsel;
-                const u4_t lo = *(const u4_t*)(&lds[buf][1][chunk(rr, kc)]);
-                const u4_t hi = *(const u4_t*)(&lds[buf][1][chunk(rr, kc + 1)]);
-                bq[cf] = i8_t{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-            }
-            __builtin_amdgcn_s_setprio(1);
-#pragma unroll
-            for (int rb = 0; rb < 8; ++rb) {
-                const int rr = wm * 128 + rb * 16 + rsel;
-                const u4_t lo = *(const u4_t*)(&lds[buf][0][chunk(rr, kc)]);
-                const u4_t hi = *(const u4_t*)(&lds[buf][0][chunk(rr, kc + 1)]);
-                const i8_t aq = i8_t{(int)lo[0], (int)lo[1], (int)lo[2], (int)lo[3], (int)hi[0], (int)hi[1], (int)hi[2], (int)hi[3]};
-#pragma unroll
-                for (int cf = 0; cf < 4; ++cf)
-                    acc[rb][cf] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(aq, bq[cf], acc[rb][cf], 0, 0, 0, 0,
-                                                                                  0, 0);
-            }
-            __builtin_amdgcn_s_setprio(0);
-        }
-    }
-
-    // no copy may land after the workgroup's LDS is released
-    __builtin_amdgcn_s_waitcnt(0);
-
-    if (idle) return;
-    if (nparts > 1) {  // raw FP32 partial tile
-        float* pt = part + (int64_t)(tq * nparts + tp) * BT * BT;
-#pragma unroll
-        for (int rb = 0; rb < 8; ++rb)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int cf = 0; cf < 4; ++cf)
-                    pt[(wm * 128 + rb * 16 + 4 * (lane >> 4) + e) * BT + wn * 64 + cf * 16 + (lane & 15)] = acc[rb][cf][e];
-        return;
-    }
-#pragma unroll
-    for (int rb = 0; rb < 8; ++rb) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const int gi = i0 + wm * 128 + rb * 16 + 4 * (lane >> 4) + e;
-            if (gi >= t.dM) continue;
-            const int64_t rowbase = packed_index((int64_t)t.r0 + gi, t.q0);
-            const double si = 1.0 / (double)scale[tx.col + gi];
-#pragma unroll
-            for (int cf = 0; cf < 4; ++cf) {
-                const int gj = j0 + wn * 64 + cf * 16 + (lane & 15);
-                if (gj >= t.dN || (syrk && gj > gi)) continue;
-                const double v = (double)acc[rb][cf][e] * si / (double)scale[ty.col + gj];  // exact power-of-two de-scale
-                if (t.dst == 0)
-                    store_out(C + rowbase + gj, t.beta, v);
-                else
-                    W[t.ws_off + (int64_t)gi * t.N + gj] = v;
-            }
-        }
-    }
-}
-
-// Sum of the K parts of the split last-round tiles (FP64, in part order),
-// de-scaled and stored as k_lp8_big stores: block (li, q) covers row li of
-// tail tile q, one thread per column.
-__global__ void __launch_bounds__(256) k_lp8_tail_sum(const float* __restrict__ scale,
-                                                     const DevTask* __restrict__ tasks,
-                                                     const DevTerm* __restrict__ terms,
-                                                     const WorkItem* __restrict__ tail, int nparts,
-                                                     const float* __restrict__ part, double* __restrict__ C,
-                                                     double* __restrict__ W) {
-    const int q = blockIdx.y, li = blockIdx.x, lj = threadIdx.x;
-    const WorkItem w = tail[q * nparts];
-    const DevTask t = tasks[w.task];
-    const int gi = w.ti * BT + li, gj = w.tj * BT + lj;
-    if (gi >= t.dM || gj >= t.dN || (t.kind == TK_SYRK && gj > gi)) return;
-    const DevTerm tx = terms[t.term_off];
-    const DevTerm ty = terms[t.term_off + 1];
-    double v = 0.0;
-    for (int p = 0; p < nparts; ++p) v += (double)part[((int64_t)(q * nparts + p) * BT + li) * BT + lj];
-    v = v * (1.0 / (double)scale[tx.col + gi]) / (double)scale[ty.col + gj];  // exact power-of-two de-scale
-    if (t.dst == 0)
-        store_out(C + packed_index((int64_t)t.r0 + gi, t.q0) + gj, t.beta, v);
-    else
-        W[t.ws_off + (int64_t)gi * t.N + gj] = v;
 }
 
 // ---------------------------------------------------------------------------
@@ -2835,7 +2660,7 @@ hipError_t launch_colscale(const float* A, int64_t lda, int m, int n, float* par
     if (n <= 0) return hipSuccess;
     const int nch = m > 0 ? (m + 255) / 256 : 0;
     if (nch > 0) hipLaunchKernelGGL(k_colmax_part, dim3((n + 1023) / 1024, nch), dim3(256), 0, s, A, lda, m, n, part);
-    hipLaunchKernelGGL(k_colscale, dim3((n + 255) / 256), dim3(256), 0, s, part, nch, n, scale);
+    hipLaunchKernelGGL(k_colscale, dim3((n + 63) / 64), dim3(256), 0, s, part, nch, n, scale);
     return hipGetLastError();
 }
 
@@ -2873,11 +2698,12 @@ hipError_t launch_descale(bool f32, bool out_f64, void* C, int n, const void* sc
 hipError_t launch_prep_lp(int mode, const float* A, int64_t lda, int m, int n, int ldt, const float* scale,
                           void* out0, void* out1, hipStream_t s) {
     if (n <= 0 || ldt <= 0) return hipSuccess;
-    const dim3 g((ldt + 127) / 128, (n + 63) / 64);
     if (mode == 0)
-        hipLaunchKernelGGL(k_prep_lp<0>, g, dim3(256), 0, s, A, lda, m, n, ldt, scale, out0, out1);
+        hipLaunchKernelGGL(k_prep_bf16, dim3((ldt + 127) / 128, (n + 63) / 64), dim3(256), 0, s, A, lda, m, n, ldt,
+                           (uint16_t*)out0, (uint16_t*)out1);
     else
-        hipLaunchKernelGGL(k_prep_lp<1>, g, dim3(256), 0, s, A, lda, m, n, ldt, scale, out0, out1);
+        hipLaunchKernelGGL(k_prep_e4m3, dim3((ldt + 255) / 256, (n + 63) / 64), dim3(256), 0, s, A, lda, m, n, ldt,
+                           scale, (uint8_t*)out0);
     return hipGetLastError();
 }
 
@@ -2885,19 +2711,22 @@ hipError_t launch_prep_lp(int mode, const float* A, int64_t lda, int m, int n, i
 // by staging path: 2 direct-to-LDS 16-byte copies, 1 dword copies,
 // 0 through registers.
 template <int M, typename O, bool S>
-static void lp_tiles(int path, dim3 g, hipStream_t s, const uint8_t* t0, const uint8_t* t1, int ldt,
-                     const float* scale, const DevTables& tb, const WorkItem* items, void* C, double* W, int nparts,
-                     double* part) {
+static hipError_t lp_tiles(int path, dim3 g, hipStream_t s, const uint8_t* t0, const uint8_t* t1, int ldt,
+                           const float* scale, const DevTables& tb, const WorkItem* items, void* C, double* W,
+                           int nparts, double* part) {
     const dim3 b(256);
-    if (path == 2)
-        hipLaunchKernelGGL((k_gemm_lpd<M, O, S, true>), g, b, 0, s, t0, t1, ldt, scale, tb.tasks, tb.terms, tb.segs,
-                           items, (O*)C, W, nparts, part);
-    else if (path == 1)
-        hipLaunchKernelGGL((k_gemm_lpd<M, O, S, false>), g, b, 0, s, t0, t1, ldt, scale, tb.tasks, tb.terms, tb.segs,
-                           items, (O*)C, W, nparts, part);
+    if (path == 2) {
+        const int nit = (int)g.x;
+        return launch_lp_tile16(M, sizeof(O) == 8, false, LpCopy{t0, t1, ldt, scale}, tb, items, S ? 0 : nit, items,
+                                S ? nit : 0, nparts, part, C, W, s);
+    }
+    if (path == 1)
+        hipLaunchKernelGGL((k_gemm_lpd<M, O, S>), g, b, 0, s, t0, t1, ldt, scale, tb.tasks, tb.terms, tb.segs, items,
+                           (O*)C, W, nparts, part);
     else
         hipLaunchKernelGGL((k_gemm_lp<M, O, S>), g, b, 0, s, t0, t1, ldt, scale, tb.tasks, tb.terms, tb.segs, items,
                            (O*)C, W, nparts, part);
+    return hipGetLastError();
 }
 
 // Staging path for windows aligned on `align` (0: none, 1: dwords, 2: 16
@@ -2917,27 +2746,11 @@ hipError_t launch_gemm_lp(int mode, bool out_f64, const void* T0, const void* T1
     const uint8_t* t0 = (const uint8_t*)T0;
     const uint8_t* t1 = (const uint8_t*)(T1 ? T1 : T0);
     const int path = lp_path(mode, ldt, align);
-    if (mode == 0 && out_f64) lp_tiles<0, double, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
-    else if (mode == 0) lp_tiles<0, float, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
-    else if (out_f64) lp_tiles<1, double, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
-    else lp_tiles<1, float, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
-    return hipGetLastError();
-}
-
-hipError_t launch_lp8_big(const void* T0, int ldt, const float* scale, const DevTables& tb, const WorkItem* items,
-                          int nitems, double* C, double* W, hipStream_t s, int nparts, float* part) {
-    if (nitems <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lp8_big, dim3(nitems), dim3(512), 0, s, (const uint8_t*)T0, ldt, scale, tb.tasks, tb.terms,
-                       tb.segs, items, C, W, nparts, part);
-    return hipGetLastError();
-}
-
-hipError_t launch_lp8_tail_sum(const float* scale, const DevTables& tb, const WorkItem* tail, int ntiles, int nparts,
-                               const float* part, double* C, double* W, hipStream_t s) {
-    if (ntiles <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_lp8_tail_sum, dim3(kBigTile, ntiles), dim3(kBigTile), 0, s, scale, tb.tasks, tb.terms, tail,
-                       nparts, part, C, W);
-    return hipGetLastError();
+    if (mode == 0 && out_f64)
+        return lp_tiles<0, double, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
+    if (mode == 0) return lp_tiles<0, float, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
+    if (out_f64) return lp_tiles<1, double, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
+    return lp_tiles<1, float, false>(path, g, s, t0, t1, ldt, scale, tb, items, C, W, 1, nullptr);
 }
 
 hipError_t launch_gemm_lp_split(int mode, bool out_f64, const void* T0, const void* T1, int ldt, const float* scale,
@@ -2948,12 +2761,12 @@ hipError_t launch_gemm_lp_split(int mode, bool out_f64, const void* T0, const vo
     const uint8_t* t0 = (const uint8_t*)T0;
     const uint8_t* t1 = (const uint8_t*)(T1 ? T1 : T0);
     const int path = lp_path(mode, ldt, align);
-    if (mode == 0 && out_f64) lp_tiles<0, double, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
-    else if (mode == 0) lp_tiles<0, float, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
-    else if (out_f64) lp_tiles<1, double, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
-    else lp_tiles<1, float, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
-    const hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    hipError_t e;
+    if (mode == 0 && out_f64) e = lp_tiles<0, double, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
+    else if (mode == 0) e = lp_tiles<0, float, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
+    else if (out_f64) e = lp_tiles<1, double, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
+    else e = lp_tiles<1, float, true>(path, g, s, t0, t1, ldt, scale, tb, tail, C, W, nparts, part);
+    if (e != hipSuccess || path == 2) return e;  // path 2 sums its parts
     if (out_f64)
         hipLaunchKernelGGL(k_tile_part_sum<double>, gs, bs, 0, s, tb.tasks, tail, nparts, (const double*)part,
                            (double*)C, W);

@@ -170,11 +170,11 @@ struct Phase {
     std::vector<WorkItem> mix_items;
     std::vector<DevCombine> combines;
     std::vector<DevOpSum> opsums;  // run before the product tiles
-    // Reduced-precision plans: the classical tasks on 256 x 256 e4m3 tiles,
-    // and the tiles of a short last round split into big_tail_parts K parts
-    // (slot = tile * parts + part).
-    std::vector<WorkItem> big_items, big_tail;
-    int big_tail_parts = 0;
+    // Reduced-precision plans, by mode: the classical tasks on wide tiles, and
+    // the tiles of a short last round split into wide_parts K parts (slot =
+    // tile * parts + part).
+    std::vector<WorkItem> wide_items[2], wide_tail[2];
+    int wide_parts[2] = {0, 0};
     // One-term tile launches: the tiles of a short last round (taken off the
     // end of mix_items, or of the phase's one classical list for FP32) split
     // into tail_parts K parts (slot = tile * parts + part).
@@ -229,10 +229,12 @@ struct Plan {
 constexpr int kGemmTile = 128;  // TK_GEMM / TK_SYRK
 constexpr int kTileQueues = 8;  // work queues of a persistent FP64 tile launch (one per XCD)
 constexpr int kTileSlots = 512;  // resident FP64 tile workgroups (two per CU on 256 CUs)
-// e4m3 classical tiles of 256 x 256 (k_lp8_big), for launches of at least
-// kBigMinTiles of them (one per CU).
-constexpr int kBigTile = 256;
-constexpr int kBigMinTiles = 256;
+// Wide reduced-precision tiles (k_lp_tile, one workgroup per CU), for launches
+// of at least kWideMin of them: kWideRows rows, 128 columns for bfloat16
+// (mode 0) and 256 for e4m3 (mode 1).
+constexpr int kWideRows = 256;
+constexpr int kWideMin = 256;
+constexpr int wide_cols(int mode) { return mode == 0 ? 128 : 256; }
 constexpr int kStrTile = 64;    // TK_STR quadrant tile (4 quadrants per workgroup)
 // Largest row stride in bytes: kernels address a staged slab of rows with
 // 32-bit offsets.
