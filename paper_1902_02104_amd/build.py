@@ -15,7 +15,7 @@ CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libata.so")
 
 SOURCES = ["ata_plan.cpp", "ata_api.cpp", "ata_serve.cpp", "ata_solve.cpp", "ata_kernels.hip", "ata_fine.hip",
-           "ata_lp.hip", "ata_chol.hip", "ata_trsv.hip"]
+           "ata_lp.hip", "ata_chol.hip", "ata_trsv.hip", "ata_mv.hip"]
 
 
 def hipcc() -> str:

@@ -1,8 +1,6 @@
 // Consumers of the packed product on gfx950: the Cholesky factor of the
-// packed lower C (the solves with it are in ata_trsv.hip), the right-hand side A^t b
-// of the normal equations and the product A X that applies the projection
-// A (A^t A)^-1 A^t (Section 1 names both as uses of A^t A); and the transpose
-// that gives the companion product A A^t.
+// packed lower C (the solves with it are in ata_trsv.hip, A^t b and A X in
+// ata_mv.hip); and the transpose that gives the companion product A A^t.
 //
 // Storage: row-major packed lower triangle, element (i, j), j <= i, at
 // i (i + 1) / 2 + j, so a row's entries left of the diagonal are contiguous.
@@ -654,92 +652,6 @@ __global__ __launch_bounds__(256, UT == 128 ? 2 : 4) void k_chol_syrk(T* __restr
     }
 }
 
-// Sum of v over the 64 lanes of the wave (every lane receives it).
-template <typename T>
-__device__ __forceinline__ T wave_sum(T v) {
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-    return v;
-}
-
-constexpr int RC = 8;  // right-hand sides per pass of A^t B and A X
-
-// ---------------------------------------------------------------------------
-// A^t B: partial sums over row chunks (workgroup = 256 columns x one chunk,
-// thread = column, rows ascending, FP64 accumulation), then a pass that adds
-// the chunks in order.  Each row of A is read once per eight right-hand
-// sides, contiguously across the workgroup.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_atb_part(const T* __restrict__ A, int64_t m, int64_t n, int64_t lda,
-                                                  const T* __restrict__ B, int64_t nrhs, int64_t ldb, int64_t rows,
-                                                  double* __restrict__ part) {
-    const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t ch = blockIdx.y;
-    const int64_t i0 = ch * rows;
-    const int64_t i1 = i0 + rows < m ? i0 + rows : m;
-    for (int64_t r0 = 0; r0 < nrhs; r0 += RC) {
-        const int rc = (int)(nrhs - r0 < RC ? nrhs - r0 : RC);
-        double acc[RC];
-#pragma unroll
-        for (int rr = 0; rr < RC; ++rr) acc[rr] = 0.0;
-        if (j < n) {
-            for (int64_t i = i0; i < i1; ++i) {
-                const double a = (double)A[i * lda + j];
-#pragma unroll
-                for (int rr = 0; rr < RC; ++rr)
-                    if (rr < rc) acc[rr] += a * (double)B[i * ldb + r0 + rr];
-            }
-#pragma unroll
-            for (int rr = 0; rr < RC; ++rr)
-                if (rr < rc) part[(ch * n + j) * nrhs + r0 + rr] = acc[rr];
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------
-// A X for the projection A (A^t A)^-1 A^t B: one wave per row of A (four rows
-// per workgroup), lanes striding the row's n entries (contiguous loads), FP64
-// sums over lanes and a wave-wide sum per right-hand side.  X (n x nrhs) is
-// small and read through the caches.
-// ---------------------------------------------------------------------------
-template <typename T>
-__global__ __launch_bounds__(256) void k_ax(const T* __restrict__ A, int64_t m, int64_t n, int64_t lda,
-                                            const T* __restrict__ X, int64_t nrhs, int64_t ldx, T* __restrict__ out,
-                                            int64_t ldo) {
-    const int lane = threadIdx.x & 63;
-    const int64_t i = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (i >= m) return;  // whole waves leave; no barrier follows
-    const T* a = A + i * lda;
-    for (int64_t r0 = 0; r0 < nrhs; r0 += RC) {
-        const int rc = (int)(nrhs - r0 < RC ? nrhs - r0 : RC);
-        double acc[RC];
-#pragma unroll
-        for (int rr = 0; rr < RC; ++rr) acc[rr] = 0.0;
-#pragma unroll 4
-        for (int64_t j = lane; j < n; j += 64) {
-            const double v = (double)a[j];
-#pragma unroll
-            for (int rr = 0; rr < RC; ++rr)
-                if (rr < rc) acc[rr] += v * (double)X[j * ldx + r0 + rr];
-        }
-        for (int rr = 0; rr < rc; ++rr) {
-            const double sum = wave_sum(acc[rr]);
-            if (lane == 0) out[i * ldo + r0 + rr] = (T)sum;
-        }
-    }
-}
-
-template <typename T>
-__global__ __launch_bounds__(256) void k_atb_sum(const double* __restrict__ part, int64_t chunks, int64_t n,
-                                                 int64_t nrhs, T* __restrict__ out, int64_t ldo) {
-    const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (e >= n * nrhs) return;
-    double s = 0.0;
-    for (int64_t c = 0; c < chunks; ++c) s += part[c * n * nrhs + e];
-    out[(e / nrhs) * ldo + e % nrhs] = (T)s;
-}
-
 // The factorization on s with a helper stream s2 and two events.  Ordering:
 // the rest of the update after panel p waits for the panel (event e); the
 // next panel's part of the update after panel p + 1 waits for the rest of the
@@ -805,20 +717,6 @@ hipError_t potrf_t(T* C, int64_t n, int32_t* info, T* ws, hipStream_t s, hipStre
     return hipSuccess;
 }
 
-template <typename T>
-hipError_t atb_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int64_t nrhs, int64_t ldb, T* out,
-                 int64_t ldo, double* part, int64_t chunks, hipStream_t s) {
-    const int64_t rows = (m + chunks - 1) / chunks;
-    ProfScope ps(ATA_KERNEL_SOLVE, s);
-    hipLaunchKernelGGL(k_atb_part<T>, dim3((unsigned)((n + 255) / 256), (unsigned)chunks), dim3(256), 0, s, A, m, n,
-                       lda, B, nrhs, ldb, rows, part);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_atb_sum<T>, dim3((unsigned)((n * nrhs + 255) / 256)), dim3(256), 0, s, part, chunks, n, nrhs,
-                       out, ldo);
-    return hipGetLastError();
-}
-
 // ---------------------------------------------------------------------------
 // Transpose for the companion product A A^t: out (n x m, row stride m) =
 // A^t for A (m x n, row stride lda), 64 x 64 tiles through LDS so that both
@@ -846,19 +744,6 @@ __global__ __launch_bounds__(256) void k_transpose(const E* __restrict__ A, int6
 
 }  // namespace
 
-hipError_t launch_ax(bool f32, const void* A, int64_t m, int64_t n, int64_t lda, const void* X, int64_t nrhs,
-                     int64_t ldx, void* out, int64_t ldo, hipStream_t s) {
-    ProfScope ps(ATA_KERNEL_SOLVE, s);
-    const dim3 grid((unsigned)((m + 3) / 4));
-    if (f32)
-        hipLaunchKernelGGL(k_ax<float>, grid, dim3(256), 0, s, (const float*)A, m, n, lda, (const float*)X, nrhs,
-                           ldx, (float*)out, ldo);
-    else
-        hipLaunchKernelGGL(k_ax<double>, grid, dim3(256), 0, s, (const double*)A, m, n, lda, (const double*)X, nrhs,
-                           ldx, (double*)out, ldo);
-    return hipGetLastError();
-}
-
 hipError_t launch_transpose(int elem_bytes, const void* A, int64_t m, int64_t n, int64_t lda, void* out,
                             hipStream_t s) {
     const dim3 grid((unsigned)((n + 63) / 64), (unsigned)((m + 63) / 64));
@@ -877,21 +762,6 @@ hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, void* ws, h
                         hipEvent_t e, hipEvent_t f) {
     return f32 ? potrf_t((float*)C, n, info, (float*)ws, s, s2, e, f)
                : potrf_t((double*)C, n, info, (double*)ws, s, s2, e, f);
-}
-
-int64_t atb_chunks(int64_t m, int64_t n) {
-    const int64_t ct = (n + 255) / 256;
-    int64_t ch = (2048 + ct - 1) / ct;
-    const int64_t most = (m + 255) / 256;
-    if (ch > most) ch = most;
-    return ch < 1 ? 1 : ch;
-}
-
-hipError_t launch_atb(bool f32, const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs,
-                      int64_t ldb, void* out, int64_t ldo, double* part, hipStream_t s) {
-    const int64_t ch = atb_chunks(m, n);
-    return f32 ? atb_t((const float*)A, m, n, lda, (const float*)B, nrhs, ldb, (float*)out, ldo, part, ch, s)
-               : atb_t((const double*)A, m, n, lda, (const double*)B, nrhs, ldb, (double*)out, ldo, part, ch, s);
 }
 
 }  // namespace atalib

@@ -67,11 +67,11 @@ int potrf_checked(void* C, int64_t n, int dtype, int32_t* info, hipStream_t s) {
 int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs, int64_t ldb, void* out,
                 int64_t ldo, int dtype, hipStream_t s) {
     if (n == 0 || nrhs == 0) return ATA_OK;
-    const size_t bytes = (size_t)atb_chunks(m, n) * (size_t)n * (size_t)nrhs * sizeof(double);
+    const int64_t chunks = atb_chunks(m, n);
     double* part = nullptr;
-    SOLVE_TRY(hipMallocAsync((void**)&part, bytes, s));
+    if (chunks > 1) SOLVE_TRY(hipMallocAsync((void**)&part, (size_t)(chunks * n * nrhs) * sizeof(double), s));
     hipError_t e = launch_atb(dtype == ATA_F32, A, m, n, lda, B, nrhs, ldb, out, ldo, part, s);
-    const hipError_t e2 = hipFreeAsync(part, s);
+    const hipError_t e2 = part ? hipFreeAsync(part, s) : hipSuccess;
     if (e == hipSuccess) e = e2;
     return e == hipSuccess ? ATA_OK : hip_fail(e);
 }
