@@ -141,6 +141,11 @@ typedef struct ata_opts {
  * stream-ordered on `stream`: Strassen products, K-split partial tiles (of
  * launches with few tiles, and of the short last round of a launch of
  * classical tiles), operand copies of the reduced-precision forms.
+ *
+ * Memory that a call allocates stream-ordered, here and below, is kept for
+ * later calls on the same stream (at most 512 MB a device; see
+ * ata_release_caches), unless the stream is being captured or is the
+ * per-thread default stream.
  */
 int ata(const void *A, int64_t m, int64_t n, int64_t lda, void *C_lower, int dtype,
         int cutoff, void *stream);
@@ -264,7 +269,9 @@ const char *ata_version(void);
 /* Release cached plans, device task tables and the library's helper
  * streams (all devices).  Waits for every device holding such tables to go
  * idle first, since queued products read them.  Products of the serving
- * loop keep their own references and are not affected. */
+ * loop keep their own references and are not affected.  Also frees the
+ * scratch memory kept for later calls (at most 512 MB a device), after the
+ * work that used it. */
 void ata_release_caches(void);
 
 /*
@@ -442,7 +449,7 @@ int ata_normal_solve(const void *A, int64_t m, int64_t n, int64_t lda, const voi
  * ata_project: out = P B for the projection P = A (A^t A)^-1 A^t onto the
  *   column space of A, which the introduction names beside the normal
  *   equations: ata_normal_solve into a stream-ordered n x nrhs workspace,
- *   then A X (one wave per row of A, FP64 sums).  B, out: row-major
+ *   then A X (FP64 sums).  B, out: row-major
  *   m x nrhs (row strides ldb, ldo >= nrhs).  info as for ata_potrf.
  *   n = 0 gives zeros.
  */

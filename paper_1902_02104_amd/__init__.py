@@ -216,8 +216,9 @@ def profile_collect() -> dict:
 
 
 def release_caches() -> None:
-    """Free cached plans, their device tables and helper streams (waits for
-    the devices that hold them to go idle)."""
+    """Free cached plans, their device tables, helper streams and the scratch
+    memory kept for later calls (waits for the devices that hold them to go
+    idle)."""
     load().ata_release_caches()
 
 

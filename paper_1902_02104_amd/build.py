@@ -14,8 +14,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libata.so")
 
-SOURCES = ["ata_plan.cpp", "ata_api.cpp", "ata_serve.cpp", "ata_solve.cpp", "ata_kernels.hip", "ata_fine.hip",
-           "ata_lp.hip", "ata_chol.hip", "ata_trsv.hip", "ata_mv.hip"]
+SOURCES = ["ata_plan.cpp", "ata_api.cpp", "ata_serve.cpp", "ata_solve.cpp", "ata_scratch.cpp",
+           "ata_kernels.hip", "ata_fine.hip", "ata_lp.hip", "ata_chol.hip", "ata_trsv.hip", "ata_mv.hip"]
 
 
 def hipcc() -> str:

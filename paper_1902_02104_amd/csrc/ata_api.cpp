@@ -834,22 +834,20 @@ int ata_ex(const void* A, int64_t m, int64_t n, int64_t lda, void* C_lower, int 
     const WsLayout L = ws_layout(m, n, dtype, P.ws_elems, want_equilibrate(flags, P, dtype), P.opsum_elems, P.lp_ops_rows, P.lp_ops_k);
     if (L.ldt > INT32_MAX) return ATA_EUNSUPPORTED;
     char* ws = nullptr;
-    bool owned = false;
+    Scratch own;
     if (L.total) {
         if (workspace) {
             if (ws_bytes < L.total) return ATA_EWORKSPACE;
             if ((uintptr_t)workspace % 256) return -10;
             ws = (char*)workspace;
         } else {
-            HIP_TRY(hipMallocAsync((void**)&ws, L.total, s));
-            owned = true;
+            HIP_TRY(scratch_get(own, L.total, s));
+            ws = (char*)own.p;
         }
     }
     hipError_t err = enqueue_product(*pd, pd->blob, L, A, m, n, lda, C_lower, dtype, variant, ws, s, dev);
-    if (owned) {
-        hipError_t e2 = hipFreeAsync(ws, s);
-        if (err == hipSuccess) err = e2;
-    }
+    const hipError_t e2 = scratch_put(own, s);
+    if (err == hipSuccess) err = e2;
     if (err != hipSuccess) return hip_fail(err);
     return ATA_OK;
 }
@@ -963,21 +961,19 @@ int ata_aat(const void* A, int64_t m, int64_t n, int64_t lda, void* C_lower, int
     if (!current_device_ok()) return ATA_EUNSUPPORTED;
     if (m == 0) return ATA_OK;
     hipStream_t s = (hipStream_t)stream;
-    void* At = nullptr;
+    Scratch At;
     if (n > 0) {
-        HIP_TRY(hipMallocAsync(&At, (size_t)n * (size_t)m * eb, s));
-        const hipError_t e = launch_transpose(eb, A, m, n, lda, At, s);
+        HIP_TRY(scratch_get(At, (size_t)n * (size_t)m * eb, s));
+        const hipError_t e = launch_transpose(eb, A, m, n, lda, At.p, s);
         if (e != hipSuccess) {
-            (void)hipFreeAsync(At, s);
+            (void)scratch_put(At, s);
             return hip_fail(e);
         }
     }
     // A A^t is the product of the n x m matrix A^t with itself: C = (A^t)^t A^t
-    int rc = ata_ex(At, n, m, m, C_lower, dtype, cutoff, stream, nullptr, nullptr, 0);
-    if (At) {
-        const hipError_t e2 = hipFreeAsync(At, s);
-        if (rc == ATA_OK && e2 != hipSuccess) rc = hip_fail(e2);
-    }
+    int rc = ata_ex(At.p, n, m, m, C_lower, dtype, cutoff, stream, nullptr, nullptr, 0);
+    const hipError_t e2 = scratch_put(At, s);
+    if (rc == ATA_OK && e2 != hipSuccess) rc = hip_fail(e2);
     return rc;
 }
 
@@ -1045,6 +1041,7 @@ void ata_release_caches(void) {
     g_plan_lru.clear();
     g_plan_pos.clear();
     release_lookahead();
+    release_scratch();
 }
 
 }  // extern "C"

@@ -133,5 +133,17 @@ hipError_t enqueue_product(const PlanDev& pd, const char* dblob, const WsLayout&
                            int64_t n, int64_t lda, void* C_lower, int dtype, int variant, char* ws, hipStream_t s,
                            int dev, bool fork_ok = true);
 
+// Device memory of one call on stream s (ata_scratch.cpp): get before the
+// first launch that uses it, put after the last.  p is null after a failed get.
+struct Scratch {
+    void* p = nullptr;
+    size_t bytes = 0;
+    hipEvent_t ev = nullptr;
+    int dev = 0;
+};
+hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s);
+hipError_t scratch_put(Scratch& sc, hipStream_t s);
+void release_scratch();
+
 }  // namespace detail
 }  // namespace atalib

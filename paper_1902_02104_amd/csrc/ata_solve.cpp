@@ -56,10 +56,10 @@ int potrf_checked(void* C, int64_t n, int dtype, int32_t* info, hipStream_t s) {
         SOLVE_TRY(hipEventCreateWithFlags(&nl.f, hipEventDisableTiming));
         la = nl;
     }
-    void* ws = nullptr;
-    SOLVE_TRY(hipMallocAsync(&ws, potrf_ws_bytes(), s));
-    hipError_t e = launch_potrf(dtype == ATA_F32, C, n, info, ws, s, la.s2, la.e, la.f);
-    const hipError_t e2 = hipFreeAsync(ws, s);
+    Scratch ws;
+    SOLVE_TRY(scratch_get(ws, potrf_ws_bytes(), s));
+    hipError_t e = launch_potrf(dtype == ATA_F32, C, n, info, ws.p, s, la.s2, la.e, la.f);
+    const hipError_t e2 = scratch_put(ws, s);
     if (e == hipSuccess) e = e2;
     return e == hipSuccess ? ATA_OK : hip_fail(e);
 }
@@ -68,10 +68,10 @@ int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
                 int64_t ldo, int dtype, hipStream_t s) {
     if (n == 0 || nrhs == 0) return ATA_OK;
     const int64_t chunks = atb_chunks(m, n);
-    double* part = nullptr;
-    if (chunks > 1) SOLVE_TRY(hipMallocAsync((void**)&part, (size_t)(chunks * n * nrhs) * sizeof(double), s));
-    hipError_t e = launch_atb(dtype == ATA_F32, A, m, n, lda, B, nrhs, ldb, out, ldo, part, s);
-    const hipError_t e2 = part ? hipFreeAsync(part, s) : hipSuccess;
+    Scratch part;
+    if (chunks > 1) SOLVE_TRY(scratch_get(part, (size_t)(chunks * n * nrhs) * sizeof(double), s));
+    hipError_t e = launch_atb(dtype == ATA_F32, A, m, n, lda, B, nrhs, ldb, out, ldo, (double*)part.p, s);
+    const hipError_t e2 = scratch_put(part, s);
     if (e == hipSuccess) e = e2;
     return e == hipSuccess ? ATA_OK : hip_fail(e);
 }
@@ -79,10 +79,10 @@ int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
 int potrs_checked(const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, int dtype, hipStream_t s) {
     if (n == 0 || nrhs == 0) return ATA_OK;
     const bool f32 = dtype == ATA_F32;
-    void* ws = nullptr;
-    SOLVE_TRY(hipMallocAsync(&ws, potrs_ws_bytes(f32, n, nrhs), s));
-    hipError_t e = launch_potrs(f32, L, n, B, nrhs, ldb, ws, s);
-    const hipError_t e2 = hipFreeAsync(ws, s);
+    Scratch ws;
+    SOLVE_TRY(scratch_get(ws, potrs_ws_bytes(f32, n, nrhs), s));
+    hipError_t e = launch_potrs(f32, L, n, B, nrhs, ldb, ws.p, s);
+    const hipError_t e2 = scratch_put(ws, s);
     if (e == hipSuccess) e = e2;
     return e == hipSuccess ? ATA_OK : hip_fail(e);
 }
@@ -173,13 +173,14 @@ int ata_normal_solve(const void* A, int64_t m, int64_t n, int64_t lda, const voi
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return potrf_checked(nullptr, 0, dtype, info, s);
     const size_t cbytes = (size_t)(n * (n + 1) / 2) * (dtype == ATA_F32 ? 4 : 8);
-    void* C = nullptr;
-    SOLVE_TRY(hipMallocAsync(&C, cbytes, s));
+    Scratch sc;
+    SOLVE_TRY(scratch_get(sc, cbytes, s));
+    void* C = sc.p;
     int rc = ata_ex(A, m, n, lda, C, dtype, cutoff, stream, nullptr, nullptr, 0);
     if (rc == ATA_OK) rc = potrf_checked(C, n, dtype, info, s);
     if (rc == ATA_OK) rc = atb_checked(A, m, n, lda, B, nrhs, ldb, X, ldx, dtype, s);
     if (rc == ATA_OK) rc = potrs_checked(C, n, X, nrhs, ldx, dtype, s);
-    const hipError_t ef = hipFreeAsync(C, s);
+    const hipError_t ef = scratch_put(sc, s);
     if (rc == ATA_OK && ef != hipSuccess) rc = hip_fail(ef);
     return rc;
 }
@@ -213,14 +214,15 @@ int ata_project(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
         }
         return rc;
     }
-    void* X = nullptr;
-    SOLVE_TRY(hipMallocAsync(&X, (size_t)n * (size_t)nrhs * (dtype == ATA_F32 ? 4 : 8), s));
+    Scratch sc;
+    SOLVE_TRY(scratch_get(sc, (size_t)n * (size_t)nrhs * (dtype == ATA_F32 ? 4 : 8), s));
+    void* X = sc.p;
     int rc = ata_normal_solve(A, m, n, lda, B, nrhs, ldb, X, nrhs, dtype, cutoff, info, stream);
     if (rc == ATA_OK) {
         const hipError_t e = launch_ax(dtype == ATA_F32, A, m, n, lda, X, nrhs, nrhs, out, ldo, s);
         if (e != hipSuccess) rc = hip_fail(e);
     }
-    const hipError_t ef = hipFreeAsync(X, s);
+    const hipError_t ef = scratch_put(sc, s);
     if (rc == ATA_OK && ef != hipSuccess) rc = hip_fail(ef);
     return rc;
 }
