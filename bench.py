@@ -521,8 +521,9 @@ def _normal_equations(P, torch, dev, stream, C0, n: int, steps: int):
     t_solve = timed(lambda: P.cholesky_solve(Cw, b.clone(), stream=stream), steps)
     x = P.cholesky_solve(Cw, b.clone(), stream=stream)
     torch.cuda.synchronize(dev)
-    # the update kernel, timed by events on its own launch streams: C is read
-    # and written once per trailing lower entry (16 B) for 2 w flops
+    # the trailing updates after each panel of 256 columns, timed by events on
+    # their own launch streams: C is read and written once per trailing lower
+    # entry (16 B) for 2 * 256 flops
     P.profile_enable(True)
     P.profile_collect()
     for _ in range(steps):
@@ -532,14 +533,14 @@ def _normal_equations(P, torch, dev, stream, C0, n: int, steps: int):
     prof = P.profile_collect()
     P.profile_enable(False)
     upd_ms, upd_launches = prof["factor_update"]
-    entries = sum((n - kb - min(64, n - kb)) * (n - kb - min(64, n - kb) + 1) // 2 for kb in range(0, n, 64))
-    upd_bytes = 16.0 * entries * steps
-    achieved = upd_bytes / (upd_ms * 1e-3) / 1e9
-    roof_fac = {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
-                "frac": achieved / HBM_PEAK_GBS, "traffic": None, "kernel": "k_chol_update_f64",
-                "algorithmic_bytes_per_launch": upd_bytes / max(upd_launches, 1),
+    entries = sum((n - pe) * (n - pe + 1) // 2 for pe in range(256, n, 256))
+    upd_flops = 2.0 * 256 * entries * steps
+    achieved = upd_flops / (upd_ms * 1e-3) / 1e12
+    roof_fac = {"bound": "mfma", "achieved": achieved, "peak": FP64_PEAK_TFLOPS, "unit": "TFLOP/s",
+                "frac": achieved / FP64_PEAK_TFLOPS, "traffic": None, "kernel": "k_chol_syrk_f64",
+                "algorithmic_flops_per_launch": upd_flops / max(upd_launches, 1),
+                "algorithmic_bytes_per_launch": 16.0 * entries * steps / max(upd_launches, 1),
                 "avg_launch_ms": upd_ms / max(upd_launches, 1),
-                "mfma_tflops": 2 * 64 * entries * steps / (upd_ms * 1e-3) / 1e12,
                 "panel_ms_per_factor": prof["factor_panel"][0] / steps}
     out["factor"] = {"n": n, "ms": t_fac, "tflops": n ** 3 / 3 / (t_fac * 1e-3) / 1e12, "roofline": roof_fac,
                      "frac_of_fp64_peak": n ** 3 / 3 / (t_fac * 1e-3) / 1e12 / FP64_PEAK_TFLOPS,

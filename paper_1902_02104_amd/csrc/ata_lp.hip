@@ -28,10 +28,10 @@
 // of bfloat16 and the 32-row ones of e4m3 (SQ_LDS_BANK_CONFLICT is 0).
 //
 // Measured, C in float, per call with the conversions (before: 128 x 128
-// tiles of four waves): bfloat16 pairs 8192 x 8192 1955 -> 1620 us, 3001 x
-// 4000 217 -> 173 us, 262144 x 300 374 -> 343 us; e4m3 8192 x 8192 505 -> 395
-// us, 3001 x 4000 122 -> 88 us, 262144 x 300 502 -> 224 us (the last two and
-// 110 us of the first by the conversion passes).
+// tiles of four waves): bfloat16 pairs 8192 x 8192 1955 -> 1615 us, 3001 x
+// 4000 217 -> 175 us, 262144 x 300 374 -> 342 us; e4m3 8192 x 8192 503 -> 384
+// us, 3001 x 4000 122 -> 84 us, 262144 x 300 502 -> 235 us (the last two and
+// half of the first by the conversion passes).
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
