@@ -153,9 +153,11 @@ int ata(const void *A, int64_t m, int64_t n, int64_t lda, void *C_lower, int dty
 /*
  * ata_aat: the companion product C_lower = lower(A A^t), m x m packed, for
  *   the same row-major A (m x n, row stride lda >= n).  A A^t is the product
- *   of the n x m matrix A^t with itself, so the call writes A^t into a
- *   stream-ordered workspace (n x m elements, one pass over A) and runs ata
- *   on it with default options; every dtype of ata is accepted.  Argument
+ *   of the n x m matrix A^t with itself, planned as ata plans that with
+ *   default options.  Plans of fine tiles (FP64 and FP32, up to about 4000
+ *   rows) read the rows of A as they are; for others the call writes A^t into
+ *   a stream-ordered workspace (n x m elements, one pass over A) and runs ata
+ *   on it.  Every dtype of ata is accepted.  Argument
  *   codes as for ata (C_lower holds m (m + 1) / 2 elements).
  */
 int ata_aat(const void *A, int64_t m, int64_t n, int64_t lda, void *C_lower, int dtype, int cutoff, void *stream);

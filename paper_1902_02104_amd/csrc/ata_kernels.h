@@ -26,9 +26,10 @@ hipError_t launch_gemm(bool f32, bool out_f64, const void* A, int64_t lda, const
 // lower(A^t A) of K rows and n columns (packed C, beta 1 accumulates) on
 // tb x tb tiles (64 or 32), the rows in `parts` parts of `rows` rows; more
 // than one part writes FP64 partial tiles to `part` (tiles x parts x tb^2
-// doubles) and sums them in a second launch.
+// doubles) and sums them in a second launch.  by_rows: lower(A A^t) of n rows
+// of K elements (64 rows below 2^31 bytes).
 hipError_t launch_fine(bool f32, bool out_f64, int tb, const void* A, int64_t lda, int K, int n, int parts, int rows,
-                       void* C, int beta, double* part, hipStream_t s);
+                       void* C, int beta, double* part, hipStream_t s, bool by_rows = false);
 
 // FP64 tiles on 16-byte direct-to-LDS copies: nt = 1 for classical tiles
 // (TK_SYRK / TK_GEMM, and products on operand-sum buffers through Aops),
