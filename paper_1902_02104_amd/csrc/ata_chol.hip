@@ -520,8 +520,8 @@ __global__ __launch_bounds__(256, 2) void k_chol_panel(T* __restrict__ C, int64_
 // part 2 the others.  Four waves of UT/2 x UT/2, one stage ahead; the sum is
 // formed first and subtracted once.  UT = 128 (two workgroups per CU) reads
 // each operand half as often; UT = 64 gives four times the workgroups, each
-// done in a quarter of the time: for the parts on the chain and for trailing
-// matrices of few tiles.
+// done in a quarter of the time: for the parts on the chain and for smaller
+// trailing matrices.
 // ---------------------------------------------------------------------------
 // Row a and column c of linear index b in a lower triangle of tiles.
 __device__ __forceinline__ void tri_decode(int64_t b, int64_t& a, int64_t& c) {
@@ -659,14 +659,20 @@ __global__ __launch_bounds__(256, UT == 128 ? 2 : 4) void k_chol_syrk(T* __restr
 // Trailing matrices of at most kOneLaunch 64 x 64 tiles take one launch on s:
 // it lasts no longer than the next panel's part, and the events cost more
 // than the overlap brings.
+// Beyond the next panel, trailing matrices of at most kSmallTiles 64 x 64 tiles
+// take those tiles and larger ones 128 x 128: a step waits for workgroup slots
+// that a 128 x 128 tile holds for 86 us, so the smaller tiles are faster
+// wherever the steps are the longer chain (n = 4000 2362 -> 2282 us, 6000 4119
+// -> 4031, 10000 10620 -> 10470 us), and slower where the updates are (all of
+// n = 10000 on them 11110 us); a line at 3500 or 5500 rows gains less.
 // ws: two 64 x 64 blocks.
 // Measured (FP64): a step alone takes 16 us with no panel columns to its left
 // and 6 us more for every 64 (its diagonal block alone took 67 us and the rows
 // below 51 us as launches of their own); the first update at n = 10000 takes
-// 477 us alone, 50 TFLOP/s.  Factor at n = 10000 25.9 -> 10.7 ms, of which the
+// 477 us alone, 50 TFLOP/s.  Factor at n = 10000 25.9 -> 10.5 ms, of which the
 // updates are bound by the tiles and, from about 5000 columns on, the rest by
 // the chain of steps: n = 2048 3.4 -> 1.0 ms.
-constexpr int64_t kOneLaunch = 600;
+constexpr int64_t kOneLaunch = 600, kSmallTiles = 2500;
 
 template <typename T>
 hipError_t potrf_t(T* C, int64_t n, int32_t* info, T* ws, hipStream_t s, hipStream_t s2, hipEvent_t e, hipEvent_t f) {
@@ -705,9 +711,17 @@ hipError_t potrf_t(T* C, int64_t n, int32_t* info, T* ws, hipStream_t s, hipStre
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
         {
-            const int64_t t = (n - pe + 127) / 128 - NP / 128;  // tile rows beyond the next panel
             ProfScope ps(ATA_KERNEL_FACTOR_UPDATE, s2);
-            hipLaunchKernelGGL((k_chol_syrk<T, 128>), dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, s2, C, n, pb, 2);
+            // tile rows beyond the next panel
+            if (all <= kSmallTiles) {
+                const int64_t t = t64 - NP / 64;
+                hipLaunchKernelGGL((k_chol_syrk<T, 64>), dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, s2, C, n, pb,
+                                   2);
+            } else {
+                const int64_t t = (n - pe + 127) / 128 - NP / 128;
+                hipLaunchKernelGGL((k_chol_syrk<T, 128>), dim3((unsigned)(t * (t + 1) / 2)), dim3(256), 0, s2, C, n, pb,
+                                   2);
+            }
             if ((err = hipGetLastError()) != hipSuccess) return err;
         }
         if ((err = hipEventRecord(f, s2)) != hipSuccess) return err;
