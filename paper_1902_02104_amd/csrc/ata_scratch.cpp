@@ -12,9 +12,12 @@
 // another stream, so no call ever waits for another stream's work.
 //
 // At most kKeepBytes a device (and kKeepBlocks blocks) are kept; beyond that
-// the blocks released longest ago are freed, if their work is over, or else
-// the newest.  ata_release_caches frees all of them, and so does a call that
-// finds the device's memory exhausted, before it tries again.  A block is taken off the list while a call uses it, so threads never
+// the stream's own blocks released longest ago make room, or else the newest
+// is freed at once.  ata_release_caches frees all of them, and so does a call
+// that finds the device's memory exhausted, before it tries again.  An event
+// whose stream is gone is never queried or waited for (the runtime looks at
+// the stream): only a stream of the same handle waits for it, and the release
+// waits for the device.  A block is taken off the list while a call uses it, so threads never
 // share one.  Calls under stream capture (whose memory belongs to the graph)
 // and calls on the per-thread default stream (one handle for many streams)
 // allocate as before.
@@ -77,21 +80,6 @@ bool may_keep(hipStream_t s) {
     return st == hipStreamCaptureStatusNone;
 }
 
-// Whether the last use of a kept block is over.  (Another thread may be
-// capturing a stream in global mode, where a plain query would end its
-// capture.)
-bool over(const Kept& k) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    if (hipThreadExchangeStreamCaptureMode(&mode) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    const hipError_t e = hipEventQuery(k.ev);
-    if (e != hipSuccess) (void)hipGetLastError();
-    (void)hipThreadExchangeStreamCaptureMode(&mode);
-    return e == hipSuccess;
-}
-
 }  // namespace
 
 hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
@@ -122,9 +110,9 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
     }
     if (out.p) {
         e = hipStreamWaitEvent(s, out.ev, 0);
-        if (e != hipSuccess) e = hipEventSynchronize(out.ev);
         if (e != hipSuccess) {
             (void)hipEventDestroy(out.ev);
+            (void)hipFree(out.p);  // waits for the device
             out = Scratch{};
         }
         return e;
@@ -163,8 +151,10 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
         std::lock_guard<std::mutex> lk(g_mu);
         Shelf& sh = g_shelf[dev];
         while (kept && (sh.n == kKeepBlocks || sh.bytes + mine.bytes > kKeepBytes)) {
-            kept = over(sh.b[0]);
-            if (kept) old[no++] = sh.take(0);
+            int i = 0;
+            while (i < sh.n && sh.b[i].s != s) ++i;
+            kept = i < sh.n;
+            if (kept) old[no++] = sh.take(i);
         }
         if (kept) {
             sh.b[sh.n++] = mine;
@@ -173,8 +163,9 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
     }
     if (!kept) old[no++] = mine;
     for (int i = 0; i < no; ++i) {
+        const hipError_t e0 = hipStreamWaitEvent(s, old[i].ev, 0);
         const hipError_t e1 = hipFreeAsync(old[i].p, s), e2 = hipEventDestroy(old[i].ev);
-        if (e == hipSuccess) e = e1 != hipSuccess ? e1 : e2;
+        if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1 != hipSuccess ? e1 : e2;
     }
     return e;
 }
@@ -191,8 +182,8 @@ void release_scratch() {
         }
         if (!no) continue;
         (void)hipSetDevice(d);
+        (void)hipDeviceSynchronize();
         for (int i = 0; i < no; ++i) {
-            (void)hipEventSynchronize(old[i].ev);
             (void)hipFree(old[i].p);
             (void)hipEventDestroy(old[i].ev);
         }
