@@ -155,7 +155,8 @@ size_t potrs_ws_bytes(bool f32, int64_t n, int64_t nrhs);
 hipError_t launch_potrs(bool f32, const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, void* ws,
                         hipStream_t s);
 // out (m x nrhs, row stride ldo) = A X for A m x n (row stride lda) and X
-// n x nrhs (row stride ldx), FP64 sums.
+// n x nrhs (row stride ldx, kAxPad readable elements after it), FP64 sums.
+constexpr int kAxPad = 16;
 hipError_t launch_ax(bool f32, const void* A, int64_t m, int64_t n, int64_t lda, const void* X, int64_t nrhs,
                      int64_t ldx, void* out, int64_t ldo, hipStream_t s);
 // out (n x m, row stride m) = A^t for A m x n with row stride lda; elements of

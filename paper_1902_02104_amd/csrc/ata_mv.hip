@@ -115,9 +115,47 @@ __global__ __launch_bounds__(1024) void k_atb_sum(const double* __restrict__ par
 // loaded serves four rows.  The 4 RC sums over the lanes are formed together:
 // each step halves the values a lane holds as it halves the lanes that hold
 // one, 4 RC - 1 exchanges and a few for the rest instead of six for each.
-// One row per wave: FP32 20011 x 333 x 4 38 us, now 18; FP64 20000 x 2000 x 8
-// 381 us, now 118.
+// A row of X is read RC elements at a time, past nrhs too (kAxPad elements
+// follow X; sums of those columns are dropped).
+// Bound by the reads of X through the L1s where n is small, else by A: FP32
+// 20011 x 333 x 4 38 us with a row per wave and single loads of X, now 12;
+// 20000 x 2000 x 8 587 -> 35; FP64 262144 x 2048 x 1 6.2 TB/s.
 // ---------------------------------------------------------------------------
+// RC consecutive elements at any element address, in loads of up to 16 bytes.
+typedef float f4u_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef float f2u_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef double d2u_t __attribute__((ext_vector_type(2), aligned(8)));
+template <int RC>
+__device__ __forceinline__ void load_run(const float* p, float (&o)[RC]) {
+    if constexpr (RC == 1) {
+        o[0] = p[0];
+    } else if constexpr (RC == 2) {
+        const f2u_t v = *(const f2u_t*)p;
+        o[0] = v[0];
+        o[1] = v[1];
+    } else {
+#pragma unroll
+        for (int q = 0; q < RC; q += 4) {
+            const f4u_t v = *(const f4u_t*)(p + q);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[q + k] = v[k];
+        }
+    }
+}
+template <int RC>
+__device__ __forceinline__ void load_run(const double* p, double (&o)[RC]) {
+    if constexpr (RC == 1) {
+        o[0] = p[0];
+    } else {
+#pragma unroll
+        for (int q = 0; q < RC; q += 2) {
+            const d2u_t v = *(const d2u_t*)(p + q);
+            o[q] = v[0];
+            o[q + 1] = v[1];
+        }
+    }
+}
+
 template <int HALF, int O, int N>
 __device__ __forceinline__ void lane_sums(double (&v)[N], int lane) {
     if constexpr (HALF > 0) {
@@ -146,9 +184,6 @@ __global__ __launch_bounds__(256) void k_ax(const T* __restrict__ A, int64_t m, 
 #pragma unroll
     for (int q = 0; q < R; ++q) a[q] = A + (i + q < m ? i + q : m - 1) * lda;
     for (int64_t r0 = 0; r0 < nrhs; r0 += RC) {
-        const T* x[RC];
-#pragma unroll
-        for (int r = 0; r < RC; ++r) x[r] = X + (r0 + r < nrhs ? r0 + r : nrhs - 1);
         double acc[N];
 #pragma unroll
         for (int k = 0; k < N; ++k) acc[k] = 0.0;
@@ -163,8 +198,11 @@ __global__ __launch_bounds__(256) void k_ax(const T* __restrict__ A, int64_t m, 
                 const bool in = j < n;
 #pragma unroll
                 for (int q = 0; q < R; ++q) v[u][q] = in ? a[q][j] : T(0);
+                if (in)
+                    load_run<RC>(X + j * ldx + r0, xv[u]);
+                else
 #pragma unroll
-                for (int r = 0; r < RC; ++r) xv[u][r] = in ? x[r][j * ldx] : T(0);
+                    for (int r = 0; r < RC; ++r) xv[u][r] = T(0);
             }
 #pragma unroll
             for (int u = 0; u < UJ; ++u)
@@ -222,8 +260,12 @@ hipError_t ax_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* X, int64
         hipLaunchKernelGGL((k_ax<T, 2>), g, b, 0, s, A, m, n, lda, X, nrhs, ldx, out, ldo);
     else if (nrhs <= 4)
         hipLaunchKernelGGL((k_ax<T, 4>), g, b, 0, s, A, m, n, lda, X, nrhs, ldx, out, ldo);
-    else
+    else if (nrhs <= 8 || sizeof(T) == 4)
         hipLaunchKernelGGL((k_ax<T, 8>), g, b, 0, s, A, m, n, lda, X, nrhs, ldx, out, ldo);
+    else
+        // FP64: half the passes over A (180786 x 576 x 9 329 -> 272 us); FP32
+        // pays more for the conversions of unused columns (182 -> 216 us)
+        hipLaunchKernelGGL((k_ax<T, 16>), g, b, 0, s, A, m, n, lda, X, nrhs, ldx, out, ldo);
     return hipGetLastError();
 }
 

@@ -215,7 +215,7 @@ int ata_project(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
         return rc;
     }
     Scratch sc;
-    SOLVE_TRY(scratch_get(sc, (size_t)n * (size_t)nrhs * (dtype == ATA_F32 ? 4 : 8), s));
+    SOLVE_TRY(scratch_get(sc, ((size_t)n * (size_t)nrhs + kAxPad) * (dtype == ATA_F32 ? 4 : 8), s));
     void* X = sc.p;
     int rc = ata_normal_solve(A, m, n, lda, B, nrhs, ldb, X, nrhs, dtype, cutoff, info, stream);
     if (rc == ATA_OK) {
