@@ -424,7 +424,8 @@ int ata_potrf(void *C_lower, int64_t n, int dtype, int32_t *info, void *stream);
  *   B: row-major n x nrhs, row stride ldb >= nrhs, overwritten by X.  One
  *   launch for each of the forward and back substitutions and up to 128
  *   right-hand sides.  Allocates a buffer of the solved values (about
- *   2 n min(nrhs, 128) elements) stream-ordered on `stream`.
+ *   2 n min(nrhs, 128) elements) stream-ordered on `stream`.  n <= 64: one
+ *   launch, no buffer.
  */
 int ata_potrs(const void *L_lower, int64_t n, void *B, int64_t nrhs, int64_t ldb, int dtype, void *stream);
 

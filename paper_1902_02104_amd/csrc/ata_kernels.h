@@ -150,7 +150,7 @@ size_t potrf_ws_bytes();
 hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, void* ws, hipStream_t s, hipStream_t s2,
                         hipEvent_t e, hipEvent_t f);
 // L L^t X = B in place, B row-major n x nrhs with row stride ldb (n, nrhs >= 1);
-// ws holds potrs_ws_bytes (256-byte aligned).
+// ws holds potrs_ws_bytes (256-byte aligned; none for n <= 64).
 size_t potrs_ws_bytes(bool f32, int64_t n, int64_t nrhs);
 hipError_t launch_potrs(bool f32, const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, void* ws,
                         hipStream_t s);

@@ -80,7 +80,8 @@ int potrs_checked(const void* L, int64_t n, void* B, int64_t nrhs, int64_t ldb, 
     if (n == 0 || nrhs == 0) return ATA_OK;
     const bool f32 = dtype == ATA_F32;
     Scratch ws;
-    SOLVE_TRY(scratch_get(ws, potrs_ws_bytes(f32, n, nrhs), s));
+    const size_t bytes = potrs_ws_bytes(f32, n, nrhs);
+    if (bytes) SOLVE_TRY(scratch_get(ws, bytes, s));
     hipError_t e = launch_potrs(f32, L, n, B, nrhs, ldb, ws.p, s);
     const hipError_t e2 = scratch_put(ws, s);
     if (e == hipSuccess) e = e2;

@@ -330,6 +330,38 @@ __global__ __launch_bounds__(512) void k_trsv(const T* __restrict__ L, int64_t n
     if (second) solve();
 }
 
+// Both substitutions for n <= NB: one diagonal block, a wave per right-hand
+// side (lane = row), no values to pass between workgroups.  Same arithmetic as
+// k_trsv.  Bound by its launch: FP32 n = 24, two right-hand sides 23 us a call
+// with the general launches and their workspace, now 14 (18 as two launches of
+// one wave).
+template <typename T>
+__global__ __launch_bounds__(512) void k_trsv_one(const T* __restrict__ L, int n, T* __restrict__ B, int64_t nrhs,
+                                                  int64_t ldb) {
+    constexpr int LS = NB + 1;
+    __shared__ T lf[NB * LS], lb[NB * LS];
+    __shared__ T rcp[NB];
+    const int t = threadIdx.x, lane = t & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(t >> 6);
+    const int64_t r = (int64_t)blockIdx.x * 8 + wv;
+    if (t < NB) rcp[t] = t < n ? T(1) / L[pidx(t, t)] : T(1);
+    T x = T(0);
+    if (r < nrhs && lane < n) x = B[lane * ldb + r];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < NB / 8; ++u) {
+        const int row = 8 * u + wv;
+        const T v = (row < n && lane < row) ? L[pidx(row, lane)] : T(0);
+        lf[row * LS + lane] = v * rcp[lane];
+        lb[row * LS + lane] = v * rcp[row];
+    }
+    __syncthreads();
+    if (r >= nrhs) return;
+    x = substitute<T, true>(lf, lane, x) * rcp[lane];
+    x = substitute<T, false>(lb, lane, lane < n ? x : T(0)) * rcp[lane];
+    if (lane < n) B[lane * ldb + r] = x;
+}
+
 constexpr int64_t kPass = 128;  // right-hand sides solved together (bounds the workspace)
 
 template <typename T, int RC>
@@ -361,6 +393,15 @@ int rhs_group(int64_t nrhs) { return nrhs == 1 ? 1 : nrhs == 2 ? 2 : 4; }
 template <typename T>
 hipError_t potrs_passes(const T* L, int64_t n, T* B, int64_t nrhs, int64_t ldb, void* ws, hipStream_t s) {
     ProfScope ps(ATA_KERNEL_SOLVE, s);
+    if (n <= NB) {
+        for (int64_t r = 0; r < nrhs; r += (int64_t)1 << 30) {
+            const int64_t k = nrhs - r < ((int64_t)1 << 30) ? nrhs - r : (int64_t)1 << 30;
+            hipLaunchKernelGGL(k_trsv_one<T>, dim3((unsigned)((k + 7) / 8)), dim3(512), 0, s, L, (int)n, B + r, k, ldb);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     for (int64_t r = 0; r < nrhs; r += kPass) {
         const int64_t k = nrhs - r < kPass ? nrhs - r : kPass;
         const int rc = rhs_group(k);
@@ -375,6 +416,7 @@ hipError_t potrs_passes(const T* L, int64_t n, T* B, int64_t nrhs, int64_t ldb, 
 }  // namespace
 
 size_t potrs_ws_bytes(bool f32, int64_t n, int64_t nrhs) {
+    if (n <= NB) return 0;
     const int64_t k = nrhs < kPass ? nrhs : kPass, rc = rhs_group(k), np = (n + 2 * NB - 1) / (2 * NB) * (2 * NB);
     return 256 + (size_t)(2 * np * ((k + rc - 1) / rc * rc)) * (f32 ? 4 : 8);
 }
