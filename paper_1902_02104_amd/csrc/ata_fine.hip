@@ -293,7 +293,8 @@ __device__ __forceinline__ void store_c(OUT* p, int beta, double v) {
     *p = beta ? (OUT)((double)*p + v) : (OUT)v;
 }
 
-// One workgroup: tile `tile` of rows [part * rows, min(K, (part + 1) * rows)).
+// One workgroup: tile `tile` of rows [part * rows, part_end(K, part * rows, rows))
+// (every part has rows).
 // ROWS: A holds the operand columns as rows of K elements (A A^t).
 template <typename T, typename OUT, int TB, bool ROWS>
 __global__ void __launch_bounds__(256, 2) k_fine(const T* __restrict__ A, int64_t lda, int K, int n, int tiles,
@@ -313,8 +314,8 @@ __global__ void __launch_bounds__(256, 2) k_fine(const T* __restrict__ A, int64_
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool diag = ti == tj;
     const int ra = part * rows;
-    const int rb = ra + rows < K ? ra + rows : K;
-    const int nst = rb > ra ? (rb - ra + KS - 1) / KS : 0;
+    const int rb = part_end(K, ra, rows);
+    const int nst = part_stages(rb - ra, KS);
     const int64_t row_bytes = lda * (int64_t)sizeof(T);
 
     // This lane's chunk of a copy: row lane / CH of the copy's RPC rows,

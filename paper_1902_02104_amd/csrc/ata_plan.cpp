@@ -949,7 +949,7 @@ bool fine_plan(Plan& P) {
     const int64_t tl = (n + tb - 1) / tb, tiles = tl * (tl + 1) / 2;
     P.fine_tb = tb;
     P.fine_parts = (int32_t)parts;
-    P.fine_rows = (int32_t)rows;
+    P.fine_rows = (int32_t)std::min(rows, k);  // one part: rows is k rounded up to a stage
     P.fine_row = sg[kSegHdr] + sg[1];
     P.fine_k = (int32_t)k;
     P.fine_beta = o.accumulate ? 1 : t.beta;

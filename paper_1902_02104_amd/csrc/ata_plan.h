@@ -235,6 +235,11 @@ constexpr int kTileSlots = 512;  // resident FP64 tile workgroups (two per CU on
 constexpr int kWideRows = 256;
 constexpr int kWideMin = 256;
 constexpr int wide_cols(int mode) { return mode == 0 ? 128 : 256; }
+// Rows of a fine-tile part (k_fine): part p of K rows starts at p * rows and
+// ends at part_end; stages of ks rows.  K goes up to INT32_MAX and parts x rows
+// is K rounded up, so nothing here is formed past K.
+constexpr int part_end(int K, int first, int rows) { return K - first < rows ? K : first + rows; }
+constexpr int part_stages(int rows, int ks) { return rows / ks + (rows % ks != 0); }
 constexpr int kStrTile = 64;    // TK_STR quadrant tile (4 quadrants per workgroup)
 // Largest row stride in bytes: kernels address a staged slab of rows with
 // 32-bit offsets.
