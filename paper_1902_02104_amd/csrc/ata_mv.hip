@@ -30,13 +30,14 @@ using detail::ProfScope;
 template <typename T, int RC>
 __global__ __launch_bounds__(256) void k_atb_part(const T* __restrict__ A, int64_t m, int64_t n, int64_t lda,
                                                   const T* __restrict__ B, int64_t nrhs, int64_t ldb, int64_t rows,
-                                                  double* __restrict__ part, T* __restrict__ out, int64_t ldo) {
+                                                  double* __restrict__ part, T* __restrict__ out, int64_t ldo,
+                                                  int64_t c0) {
     constexpr int U = 16, BT = 4 * U, BE = (BT * RC + 255) / 256;
     __shared__ __attribute__((aligned(16))) double bs[BT * RC];
     __shared__ double red[4][RC][64];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t j = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t j = c0 + (int64_t)blockIdx.x * 64 + lane;
     const int64_t ch = blockIdx.y;
     const int64_t i0 = ch * rows;
     const int64_t i1 = i0 + rows < m ? i0 + rows : m;
@@ -89,14 +90,16 @@ __global__ __launch_bounds__(256) void k_atb_part(const T* __restrict__ A, int64
 
 // Sum over the chunks in a fixed order: 64 consecutive elements per
 // workgroup, sixteen waves over the chunks (residues mod 16), then the waves
-// in order (FP32 20011 x 333: 79 chunks in one chain 21 us, 313 now 5).
+// in order (FP32 20011 x 333: 79 chunks in one chain 21 us, 313 now 5).  The
+// workgroups are a grid of two dimensions: sixteen threads an element reach
+// the 2^32 threads of one dimension at 2^28 elements.
 template <typename T>
 __global__ __launch_bounds__(1024) void k_atb_sum(const double* __restrict__ part, int64_t chunks, int64_t n,
                                                   int64_t nrhs, T* __restrict__ out, int64_t ldo) {
     __shared__ double red[16][64];
     const int lane = threadIdx.x & 63, g = threadIdx.x >> 6;
     const int64_t total = n * nrhs;
-    const int64_t e = (int64_t)blockIdx.x * 64 + lane;
+    const int64_t e = ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * 64 + lane;
     double s = 0.0;
     if (e < total)
 #pragma unroll 8
@@ -222,9 +225,14 @@ template <typename T, int RC>
 void part_rc(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int64_t nrhs, int64_t ldb, double* part,
              int64_t chunks, T* out, int64_t ldo, hipStream_t s) {
     const int64_t rows = (m + chunks - 1) / chunks, passes = (nrhs + RC - 1) / RC;
-    const dim3 g((unsigned)((n + 63) / 64), (unsigned)chunks, (unsigned)(passes < 16384 ? passes : 16384));
-    hipLaunchKernelGGL((k_atb_part<T, RC>), g, dim3(256), 0, s, A, m, n, lda, B, nrhs, ldb, rows, part,
-                       out, ldo);
+    // columns in slices of 2^29 (2^31 threads): a grid dimension holds less than 2^32 threads
+    constexpr int64_t kSlice = (int64_t)1 << 29;
+    for (int64_t c0 = 0; c0 < n; c0 += kSlice) {
+        const int64_t w = n - c0 < kSlice ? n - c0 : kSlice;
+        const dim3 g((unsigned)((w + 63) / 64), (unsigned)chunks, (unsigned)(passes < 16384 ? passes : 16384));
+        hipLaunchKernelGGL((k_atb_part<T, RC>), g, dim3(256), 0, s, A, m, n, lda, B, nrhs, ldb, rows, part, out, ldo,
+                           c0);
+    }
 }
 
 template <typename T>
@@ -244,8 +252,9 @@ hipError_t atb_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int6
         part_rc<T, 16>(A, m, n, lda, B, nrhs, ldb, part, ch, out, ldo, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !part) return e;
-    hipLaunchKernelGGL(k_atb_sum<T>, dim3((unsigned)((n * nrhs + 63) / 64)), dim3(1024), 0, s, part, ch, n, nrhs, out,
-                       ldo);
+    const int64_t wgs = (n * nrhs + 63) / 64, gx = wgs < (1 << 20) ? wgs : 1 << 20;
+    hipLaunchKernelGGL(k_atb_sum<T>, dim3((unsigned)gx, (unsigned)((wgs + gx - 1) / gx)), dim3(1024), 0, s, part, ch,
+                       n, nrhs, out, ldo);
     return hipGetLastError();
 }
 
