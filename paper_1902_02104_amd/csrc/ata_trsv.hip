@@ -394,8 +394,10 @@ template <typename T>
 hipError_t potrs_passes(const T* L, int64_t n, T* B, int64_t nrhs, int64_t ldb, void* ws, hipStream_t s) {
     ProfScope ps(ATA_KERNEL_SOLVE, s);
     if (n <= NB) {
-        for (int64_t r = 0; r < nrhs; r += (int64_t)1 << 30) {
-            const int64_t k = nrhs - r < ((int64_t)1 << 30) ? nrhs - r : (int64_t)1 << 30;
+        // right-hand sides in slices: 64 threads each, less than 2^32 threads a launch
+        constexpr int64_t kSlice = (int64_t)1 << 25;
+        for (int64_t r = 0; r < nrhs; r += kSlice) {
+            const int64_t k = nrhs - r < kSlice ? nrhs - r : kSlice;
             hipLaunchKernelGGL(k_trsv_one<T>, dim3((unsigned)((k + 7) / 8)), dim3(512), 0, s, L, (int)n, B + r, k, ldb);
             const hipError_t e = hipGetLastError();
             if (e != hipSuccess) return e;
