@@ -126,8 +126,8 @@ __global__ __launch_bounds__(256) void k_trsv_init(T* __restrict__ buf, int64_t 
 // Substitution with one 64 x 64 diagonal block: x (lane = row).  ld holds the
 // block with column c (backward: row c) scaled by 1 / L[c][c] and zeros
 // elsewhere, so that a step is one broadcast and one multiply-add, and rows
-// already solved subtract zeros.  (If a value is not finite, those rows turn
-// into NaN as well; the other direction would do the same to them.)
+// already solved subtract zeros.  Where a value overflows or is not finite that
+// product is a NaN in rows it must not reach: see solve_block.
 template <typename T, bool FWD>
 __device__ __forceinline__ T substitute(const T* ld, int lane, T x) {
     constexpr int LS = NB + 1;
@@ -144,6 +144,32 @@ __device__ __forceinline__ T substitute(const T* ld, int lane, T x) {
         for (int c = 0; c < 16; ++c) x -= d[b & 1][c] * lane_bcast(x, FWD ? 16 * b + c : NB - 1 - (16 * b + c));
     }
     return x;
+}
+
+// The same steps with rows already solved left out and the block's entries as
+// they are in L (first row and column d0, wd of them), for any value.
+template <typename T, bool FWD>
+__device__ __forceinline__ T column_steps(const T* __restrict__ L, int64_t d0, int wd, const T* rcp, int lane, T x) {
+#pragma clang loop unroll(disable)
+    for (int k = 0; k < wd; ++k) {
+        const int c = FWD ? k : wd - 1 - k;
+        const T xc = lane_bcast(x, c) * rcp[c];
+        if (lane == c) x = xc;
+        if (FWD ? lane > c && lane < wd : lane < c)
+            x -= L[FWD ? pidx(d0 + lane, d0 + c) : pidx(d0 + c, d0 + lane)] * xc;
+    }
+    return x;
+}
+
+// Solution of a diagonal block (lane = row; zero past its wd rows).  A value
+// that is not finite shows in its own row, so one vote over the finished rows
+// finds every block that substitute may have got wrong.
+template <typename T, bool FWD>
+__device__ __forceinline__ T solve_block(const T* ld, const T* __restrict__ L, int64_t d0, int wd, const T* rcp,
+                                         int lane, T x) {
+    T v = substitute<T, FWD>(ld, lane, x) * rcp[lane];
+    if (!__all(lane >= wd || __builtin_isfinite(v))) v = column_steps<T, FWD>(L, d0, wd, rcp, lane, x);
+    return lane < wd ? v : T(0);
 }
 
 // Workgroup: the two neighbouring 64-row diagonal blocks 2 sb and 2 sb + 1
@@ -198,8 +224,8 @@ __global__ __launch_bounds__(512) void k_trsv(const T* __restrict__ L, int64_t n
     const T* xin = out + (int64_t)r0 * np;  // solved values of the other blocks
 
     // This wave's 16 columns (rows) of the block of rows rb and columns cb.
-    // Rows past the end repeat the last row (forward: their sums are not
-    // stored; backward: their solved values are zero).
+    // Rows past the end repeat the last row forward (their sums are not stored)
+    // and are zero backward, as their solved values are.
     T lv[2][16];
     auto load = [&](int64_t rb, int64_t cb, T (&v)[16]) {
         if (FWD && !TURN) {
@@ -217,8 +243,8 @@ __global__ __launch_bounds__(512) void k_trsv(const T* __restrict__ L, int64_t n
         } else {
 #pragma unroll
             for (int u = 0; u < 16; ++u) {
-                const int64_t i = rb + 16 * w4 + u < n ? rb + 16 * w4 + u : n - 1;
-                v[u] = L[pidx(i, cb + lane)];
+                const int64_t i = rb + 16 * w4 + u;
+                v[u] = i < n ? L[pidx(i, cb + lane)] : T(0);
             }
         }
     };
@@ -306,8 +332,7 @@ __global__ __launch_bounds__(512) void k_trsv(const T* __restrict__ L, int64_t n
         if (w4 >= RC) return;
         x -= (red[h][w4 * NB + lane] + red[h][(RC + w4) * NB + lane]) +
              (red[h][(2 * RC + w4) * NB + lane] + red[h][(3 * RC + w4) * NB + lane]);
-        const T s = substitute<T, FWD>(ld[h], lane, x);
-        const T v = lane < wd ? s * rcp[NB * h + lane] : T(0);
+        const T v = solve_block<T, FWD>(ld[h], L, hb, wd, rcp + NB * h, lane, x);
         publish(out + (int64_t)(r0 + w4) * np + hb + lane, v);
         if (!second) ys[w4][lane] = v;
         if (!FWD && w4 < rc && lane < wd) B[(hb + lane) * ldb + r0 + w4] = v;
@@ -357,8 +382,8 @@ __global__ __launch_bounds__(512) void k_trsv_one(const T* __restrict__ L, int n
     }
     __syncthreads();
     if (r >= nrhs) return;
-    x = substitute<T, true>(lf, lane, x) * rcp[lane];
-    x = substitute<T, false>(lb, lane, lane < n ? x : T(0)) * rcp[lane];
+    x = solve_block<T, true>(lf, L, 0, n, rcp, lane, x);
+    x = solve_block<T, false>(lb, L, 0, n, rcp, lane, x);
     if (lane < n) B[lane * ldb + r] = x;
 }
 
