@@ -163,8 +163,7 @@ hipError_t launch_ax(bool f32, const void* A, int64_t m, int64_t n, int64_t lda,
 // elem_bytes 4 or 8.
 hipError_t launch_transpose(int elem_bytes, const void* A, int64_t m, int64_t n, int64_t lda, void* out,
                             hipStream_t s);
-// out = A^t B; part holds atb_chunks(m, n) x n x nrhs doubles (null: one chunk).
-int64_t atb_chunks(int64_t m, int64_t n);
+// out = A^t B; part holds atb_chunks(m, n, nrhs) x n x nrhs doubles (null: one chunk).
 hipError_t launch_atb(bool f32, const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs,
                       int64_t ldb, void* out, int64_t ldo, double* part, hipStream_t s);
 

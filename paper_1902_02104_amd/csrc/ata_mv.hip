@@ -224,6 +224,7 @@ __global__ __launch_bounds__(256) void k_ax(const T* __restrict__ A, int64_t m, 
 template <typename T, int RC>
 void part_rc(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int64_t nrhs, int64_t ldb, double* part,
              int64_t chunks, T* out, int64_t ldo, hipStream_t s) {
+    static_assert(RC <= kAtbPass, "");
     const int64_t rows = (m + chunks - 1) / chunks, passes = (nrhs + RC - 1) / RC;
     // columns in slices of 2^29 (2^31 threads): a grid dimension holds less than 2^32 threads
     constexpr int64_t kSlice = (int64_t)1 << 29;
@@ -238,7 +239,7 @@ void part_rc(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int64_t 
 template <typename T>
 hipError_t atb_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int64_t nrhs, int64_t ldb, T* out,
                  int64_t ldo, double* part, hipStream_t s) {
-    const int64_t ch = part ? atb_chunks(m, n) : 1;
+    const int64_t ch = part ? atb_chunks(m, n, nrhs) : 1;
     ProfScope ps(ATA_KERNEL_SOLVE, s);
     if (nrhs == 1)
         part_rc<T, 1>(A, m, n, lda, B, nrhs, ldb, part, ch, out, ldo, s);
@@ -249,7 +250,7 @@ hipError_t atb_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* B, int6
     else if (nrhs <= 8)
         part_rc<T, 8>(A, m, n, lda, B, nrhs, ldb, part, ch, out, ldo, s);
     else
-        part_rc<T, 16>(A, m, n, lda, B, nrhs, ldb, part, ch, out, ldo, s);
+        part_rc<T, kAtbPass>(A, m, n, lda, B, nrhs, ldb, part, ch, out, ldo, s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess || !part) return e;
     const int64_t wgs = (n * nrhs + 63) / 64, gx = wgs < (1 << 20) ? wgs : 1 << 20;
@@ -279,14 +280,6 @@ hipError_t ax_t(const T* A, int64_t m, int64_t n, int64_t lda, const T* X, int64
 }
 
 }  // namespace
-
-int64_t atb_chunks(int64_t m, int64_t n) {
-    const int64_t ct = (n + 63) / 64;
-    int64_t ch = (2048 + ct - 1) / ct;
-    const int64_t most = (m + 63) / 64;
-    if (ch > most) ch = most;
-    return ch < 1 ? 1 : ch;
-}
 
 hipError_t launch_atb(bool f32, const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs,
                       int64_t ldb, void* out, int64_t ldo, double* part, hipStream_t s) {

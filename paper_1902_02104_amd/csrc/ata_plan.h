@@ -235,6 +235,16 @@ constexpr int kTileSlots = 512;  // resident FP64 tile workgroups (two per CU on
 constexpr int kWideRows = 256;
 constexpr int kWideMin = 256;
 constexpr int wide_cols(int mode) { return mode == 0 ? 128 : 256; }
+// Row chunks of A^t B (k_atb_part): 2048 workgroups of 64 columns and kAtbPass
+// right-hand sides, none of less than 64 rows.  The FP64 partial sums, chunks x
+// n x nrhs, so stay near 2048 x 64 x kAtbPass (16.8 MB) however many right-hand
+// sides there are.
+constexpr int kAtbPass = 16;
+constexpr int64_t atb_chunks(int64_t m, int64_t n, int64_t nrhs) {
+    const int64_t wgs = ((n + 63) / 64) * ((nrhs + kAtbPass - 1) / kAtbPass);
+    const int64_t want = wgs > 0 ? (2048 + wgs - 1) / wgs : 1, most = (m + 63) / 64;
+    return most < 1 ? 1 : want < most ? want : most;
+}
 // Rows of a fine-tile part (k_fine): part p of K rows starts at p * rows and
 // ends at part_end; stages of ks rows.  K goes up to INT32_MAX and parts x rows
 // is K rounded up, so nothing here is formed past K.

@@ -67,7 +67,7 @@ int potrf_checked(void* C, int64_t n, int dtype, int32_t* info, hipStream_t s) {
 int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B, int64_t nrhs, int64_t ldb, void* out,
                 int64_t ldo, int dtype, hipStream_t s) {
     if (n == 0 || nrhs == 0) return ATA_OK;
-    const int64_t chunks = atb_chunks(m, n);
+    const int64_t chunks = atb_chunks(m, n, nrhs);
     Scratch part;
     if (chunks > 1) SOLVE_TRY(scratch_get(part, (size_t)(chunks * n * nrhs) * sizeof(double), s));
     hipError_t e = launch_atb(dtype == ATA_F32, A, m, n, lda, B, nrhs, ldb, out, ldo, (double*)part.p, s);

@@ -18,8 +18,7 @@ def env():
     torch.cuda.empty_cache()
 
 
-def test_atb_with_2_28_results_from_two_chunks(env):
-    """n nrhs = 2^28 entries, each the sum of two row chunks."""
+def test_atb_with_2_28_results(env):
     torch, P = env
     m, n, r = 65, 16384, 16384
     print("case: atb", m, n, r, flush=True)
