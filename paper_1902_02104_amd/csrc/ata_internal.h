@@ -95,6 +95,16 @@ struct ProfScope {
     ProfScope& operator=(const ProfScope&) = delete;
 };
 
+// Whether two row-major matrices share memory (rows x cols elements of es
+// bytes, row strides in elements).
+inline bool overlap(const void* a, int64_t arows, int64_t acols, int64_t lda, const void* b, int64_t brows,
+                    int64_t bcols, int64_t ldb, int es) {
+    if (arows <= 0 || acols <= 0 || brows <= 0 || bcols <= 0) return false;
+    const uintptr_t a0 = (uintptr_t)a, b0 = (uintptr_t)b;
+    return a0 < b0 + (uintptr_t)(((brows - 1) * ldb + bcols) * es) &&
+           b0 < a0 + (uintptr_t)(((arows - 1) * lda + acols) * es);
+}
+
 int hip_fail(hipError_t e);
 int check_device(int dev);       // caller holds the library mutex
 int current_device_ok();         // the current device is gfx950 (locks)

@@ -68,8 +68,12 @@ int atb_checked(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
                 int64_t ldo, int dtype, hipStream_t s) {
     if (n == 0 || nrhs == 0) return ATA_OK;
     const int64_t chunks = atb_chunks(m, n, nrhs);
+    // One chunk writes the results directly, unless they go over an input that
+    // other workgroups still read.
+    const int es = dtype == ATA_F32 ? 4 : 8;
+    const bool over = overlap(out, n, nrhs, ldo, B, m, nrhs, ldb, es) || overlap(out, n, nrhs, ldo, A, m, n, lda, es);
     Scratch part;
-    if (chunks > 1) SOLVE_TRY(scratch_get(part, (size_t)(chunks * n * nrhs) * sizeof(double), s));
+    if (chunks > 1 || over) SOLVE_TRY(scratch_get(part, (size_t)(chunks * n * nrhs) * sizeof(double), s));
     hipError_t e = launch_atb(dtype == ATA_F32, A, m, n, lda, B, nrhs, ldb, out, ldo, (double*)part.p, s);
     const hipError_t e2 = scratch_put(part, s);
     if (e == hipSuccess) e = e2;
