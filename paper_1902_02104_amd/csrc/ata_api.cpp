@@ -975,7 +975,12 @@ int ata_aat(const void* A, int64_t m, int64_t n, int64_t lda, void* C_lower, int
                                  plan_flags(flags, dtype), true, pd);
         if (prc != ATA_OK) return prc;
         const Plan& P = pd->plan;
-        if (P.fine_tb && P.fine_row == 0 && P.fine_k == n) {
+        // In one part tiles of C are stored while others are formed: not where
+        // C lies over A, which the transpose copies first.
+        const int ob = elem_bytes_out(dtype);
+        const bool over = P.fine_parts <= 1 &&
+                          overlap(C_lower, 1, m * (m + 1) / 2 * ob, 0, A, 1, ((m - 1) * lda + n) * eb, 0, 1);
+        if (P.fine_tb && P.fine_row == 0 && P.fine_k == n && !over) {
             Scratch part;
             if (P.fine_parts > 1) HIP_TRY(scratch_get(part, P.ws_elems * sizeof(double), s));
             ProfScope ps(ATA_KERNEL_SYRK, s);

@@ -37,6 +37,20 @@ def test_atb_over_its_right_hand_side(env, n, dt):
         assert torch.equal(X, want)
 
 
+@pytest.mark.parametrize("m,n", [(40, 30), (1000, 512), (1500, 1000), (300, 20000)])
+@pytest.mark.parametrize("dt", ["float32", "float64"])
+def test_row_products_over_their_input(env, m, n, dt):
+    """lower(A A^t) into A's own memory."""
+    torch, P = env
+    dt = getattr(torch, dt)
+    print("case: row products in place", m, n, dt, flush=True)
+    A = _ints(torch, m, n, dt, m + n)
+    buf = torch.zeros(max(m * n, P.tri(m)), dtype=dt, device="cuda")
+    buf[: m * n] = A.reshape(-1)
+    want = P.gram_rows(A)
+    P.gram_rows(buf[: m * n].reshape(m, n), out=buf[: P.tri(m)])
+    assert torch.equal(buf[: P.tri(m)], want)
+
 
 def test_wide_atb_over_its_right_hand_side(env):
     """2^28 results of one chunk through the separate sum, which has sixteen
