@@ -217,7 +217,7 @@ void serialize(PlanDev& pd) {
 
 // Copy a serialized plan into one device allocation.
 int upload(PlanDev& pd, int dev) {
-    HIP_TRY(hipMalloc(&pd.blob, pd.host_blob.size()));
+    HIP_TRY(device_alloc((void**)&pd.blob, pd.host_blob.size()));
     pd.device = dev;
     HIP_TRY(hipMemcpy(pd.blob, pd.host_blob.data(), pd.host_blob.size(), hipMemcpyHostToDevice));
     return ATA_OK;

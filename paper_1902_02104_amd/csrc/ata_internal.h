@@ -153,6 +153,8 @@ struct Scratch {
 };
 hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s);
 hipError_t scratch_put(Scratch& sc, hipStream_t s);
+// hipMalloc that gives the kept scratch back where memory has run out.
+hipError_t device_alloc(void** p, size_t bytes);
 void release_scratch();
 
 }  // namespace detail

@@ -13,12 +13,12 @@
 //
 // At most kKeepBytes a device (and kKeepBlocks blocks) are kept; beyond that
 // the stream's own blocks released longest ago make room, or else the newest
-// is freed at once.  ata_release_caches frees all of them, and so does a call
-// that finds the device's memory exhausted, before it tries again.  An event
-// whose stream is gone is never queried or waited for (the runtime looks at
-// the stream): only a stream of the same handle waits for it, and the release
-// waits for the device.  A block is taken off the list while a call uses it, so threads never
-// share one.  Calls under stream capture (whose memory belongs to the graph)
+// is freed at once.  ata_release_caches frees all of them, and so does any
+// allocation of the library outside a capture that finds the device's memory
+// exhausted, before it tries again.  An event whose stream is gone is never
+// queried or waited for (the runtime looks at the stream): only a stream of the
+// same handle waits for it, and the release waits for the device.  A block is
+// taken off the list while a call uses it, so threads never share one.  Calls under stream capture (whose memory belongs to the graph)
 // and calls on the per-thread default stream (one handle for many streams)
 // allocate as before.
 #include <hip/hip_runtime.h>
@@ -70,14 +70,27 @@ size_t block_size(size_t need) {
     return b < ((size_t)64 << 10) ? (size_t)64 << 10 : b;
 }
 
-bool may_keep(hipStream_t s) {
-    if (s == hipStreamPerThread) return false;
+// Whether s may be under capture.
+bool capturing(hipStream_t s) {
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(s, &st) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return true;
     }
-    return st == hipStreamCaptureStatusNone;
+    return st != hipStreamCaptureStatusNone;
+}
+
+// Memory from the stream's pool; where there is none left, the kept blocks go
+// back first.  (Not for a capture, which a wait for the device would break.)
+hipError_t allocate(void** p, size_t bytes, hipStream_t s, bool capture) {
+    hipError_t e = hipMallocAsync(p, bytes, s);
+    if (e == hipErrorOutOfMemory && !capture) {
+        (void)hipGetLastError();
+        release_scratch();
+        e = hipMallocAsync(p, bytes, s);
+    }
+    if (e != hipSuccess) *p = nullptr;
+    return e;
 }
 
 }  // namespace
@@ -88,9 +101,10 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     out.bytes = block_size(bytes);
-    if (out.bytes > kKeepBytes || dev < 0 || dev >= kDevices || !may_keep(s)) {
+    const bool capture = capturing(s);
+    if (out.bytes > kKeepBytes || dev < 0 || dev >= kDevices || capture || s == hipStreamPerThread) {
         out.bytes = bytes;
-        return hipMallocAsync(&out.p, bytes, s);
+        return allocate(&out.p, bytes, s, capture);
     }
     out.dev = dev;
     {
@@ -119,12 +133,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
     }
     e = hipEventCreateWithFlags(&out.ev, hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) return e;
-    e = hipMallocAsync(&out.p, out.bytes, s);
-    if (e == hipErrorOutOfMemory) {
-        (void)hipGetLastError();
-        release_scratch();
-        e = hipMallocAsync(&out.p, out.bytes, s);
-    }
+    e = allocate(&out.p, out.bytes, s, false);
     if (e != hipSuccess) {
         (void)hipEventDestroy(out.ev);
         out = Scratch{};
@@ -167,6 +176,17 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
         const hipError_t e1 = hipFreeAsync(old[i].p, s), e2 = hipEventDestroy(old[i].ev);
         if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1 != hipSuccess ? e1 : e2;
     }
+    return e;
+}
+
+hipError_t device_alloc(void** p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e == hipErrorOutOfMemory) {
+        (void)hipGetLastError();
+        release_scratch();
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) *p = nullptr;
     return e;
 }
 

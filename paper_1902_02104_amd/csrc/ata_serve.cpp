@@ -549,7 +549,7 @@ int ata_server_create(size_t budget_bytes, int max_active, int streams, int flag
         e = hipGetDeviceProperties(&p, s->dev);
         if (e != hipSuccess) return hip_fail(e);
         if (std::strncmp(p.gcnArchName, "gfx950", 6) != 0) return ATA_EUNSUPPORTED;
-        e = hipMalloc((void**)&s->base, budget_bytes);
+        e = device_alloc((void**)&s->base, budget_bytes);
         if (e != hipSuccess) return hip_fail(e);
         for (int i = 0; i < streams; ++i) {
             hipStream_t st;
