@@ -43,6 +43,7 @@ struct Kept {
     size_t bytes;
     hipEvent_t ev;
     hipStream_t s;
+    uint64_t drop;  // the release that waits for the device to free it (0: none)
 };
 
 // Blocks of one device in the order of their release.
@@ -60,6 +61,7 @@ struct Shelf {
 
 std::mutex g_mu;
 Shelf g_shelf[kDevices];
+uint64_t g_drops = 0;
 
 // Block sizes in eighths of a power of two, at least 64 KB: shapes that
 // differ a little share blocks.
@@ -68,6 +70,48 @@ size_t block_size(size_t need) {
     while (unit * 16 <= need) unit *= 2;
     const size_t b = (need + unit - 1) / unit * unit;
     return b < ((size_t)64 << 10) ? (size_t)64 << 10 : b;
+}
+
+// Frees the kept blocks of device d (and their events) after the device's
+// work.  They stay listed until the wait has ended, out of reach of calls; if it
+// is refused, as while a stream is captured, they are kept as before.
+void drop_blocks(int d) {
+    uint64_t id = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        Shelf& sh = g_shelf[d];
+        for (int i = 0; i < sh.n; ++i)
+            if (!sh.b[i].drop) {
+                if (!id) id = ++g_drops;
+                sh.b[i].drop = id;
+            }
+    }
+    if (!id) return;
+    int cur = 0;
+    (void)hipGetDevice(&cur);
+    (void)hipSetDevice(d);
+    const bool done = hipDeviceSynchronize() == hipSuccess;
+    if (!done) (void)hipGetLastError();
+    Kept old[kKeepBlocks];
+    int no = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        Shelf& sh = g_shelf[d];
+        for (int i = 0; i < sh.n;) {
+            if (sh.b[i].drop != id) {
+                ++i;
+            } else if (done) {
+                old[no++] = sh.take(i);
+            } else {
+                sh.b[i++].drop = 0;
+            }
+        }
+    }
+    for (int i = 0; i < no; ++i) {
+        (void)hipFree(old[i].p);
+        (void)hipEventDestroy(old[i].ev);
+    }
+    (void)hipSetDevice(cur);
 }
 
 // Whether s may be under capture.
@@ -112,7 +156,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
         Shelf& sh = g_shelf[dev];
         int best = -1;
         for (int i = sh.n - 1; i >= 0; --i)
-            if (sh.b[i].s == s && sh.b[i].bytes >= out.bytes && sh.b[i].bytes / 2 <= out.bytes &&
+            if (sh.b[i].s == s && !sh.b[i].drop && sh.b[i].bytes >= out.bytes && sh.b[i].bytes / 2 <= out.bytes &&
                 (best < 0 || sh.b[i].bytes < sh.b[best].bytes))
                 best = i;
         if (best >= 0) {
@@ -143,7 +187,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
 
 hipError_t scratch_put(Scratch& sc, hipStream_t s) {
     if (!sc.p) return hipSuccess;
-    const Kept mine{sc.p, sc.bytes, sc.ev, s};
+    const Kept mine{sc.p, sc.bytes, sc.ev, s, 0};
     const int dev = sc.dev;
     sc = Scratch{};
     if (!mine.ev) return hipFreeAsync(mine.p, s);
@@ -161,7 +205,7 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
         Shelf& sh = g_shelf[dev];
         while (kept && (sh.n == kKeepBlocks || sh.bytes + mine.bytes > kKeepBytes)) {
             int i = 0;
-            while (i < sh.n && sh.b[i].s != s) ++i;
+            while (i < sh.n && (sh.b[i].s != s || sh.b[i].drop)) ++i;
             kept = i < sh.n;
             if (kept) old[no++] = sh.take(i);
         }
@@ -191,24 +235,7 @@ hipError_t device_alloc(void** p, size_t bytes) {
 }
 
 void release_scratch() {
-    int cur = 0;
-    (void)hipGetDevice(&cur);
-    for (int d = 0; d < kDevices; ++d) {
-        Kept old[kKeepBlocks];
-        int no = 0;
-        {
-            std::lock_guard<std::mutex> lk(g_mu);
-            while (g_shelf[d].n > 0) old[no++] = g_shelf[d].take(0);
-        }
-        if (!no) continue;
-        (void)hipSetDevice(d);
-        (void)hipDeviceSynchronize();
-        for (int i = 0; i < no; ++i) {
-            (void)hipFree(old[i].p);
-            (void)hipEventDestroy(old[i].ev);
-        }
-    }
-    (void)hipSetDevice(cur);
+    for (int d = 0; d < kDevices; ++d) drop_blocks(d);
 }
 
 }  // namespace detail

@@ -168,11 +168,25 @@ static int oom_capture() {
     REQUIRE(model::used >= 400 * MB && model::syncs == 0);
     return 0;
 }
+// While another stream captures, the device cannot be waited for: nothing is freed.
+static int refused_wait() {
+    hipStream_t s = model::make(), t = model::make(), c = model::make();
+    model::limit = 1000 * MB;
+    if (fill(s)) return 1;
+    c->capturing = true;
+    REQUIRE(call(t, 900 * MB) == hipErrorOutOfMemory);
+    release_scratch();
+    REQUIRE(model::used >= 400 * MB);
+    c->capturing = false;
+    REQUIRE(call(t, 900 * MB) == hipSuccess);
+    return 0;
+}
 int main(int, char** v) {
     if (!strcmp(v[1], "reuse")) return reuse();
     if (!strcmp(v[1], "bound")) return bound();
     if (!strcmp(v[1], "oom")) return oom();
     if (!strcmp(v[1], "oom_capture")) return oom_capture();
+    if (!strcmp(v[1], "refused_wait")) return refused_wait();
     return 2;
 }
 """
@@ -190,7 +204,7 @@ def model(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["reuse", "bound", "oom", "oom_capture"])
+@pytest.mark.parametrize("case", ["reuse", "bound", "oom", "oom_capture", "refused_wait"])
 def test_kept_scratch(model, case):
     r = subprocess.run([model, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
