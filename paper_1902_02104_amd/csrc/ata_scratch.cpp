@@ -8,21 +8,27 @@
 // recorded at the release and waited for at the reuse covers a stream handle
 // that was destroyed and created again (with it 6.6 us).  A^t B of FP32
 // 1000 x 77: 38 -> 17 us a call; the first e4m3 product after a
-// synchronisation, 8192 x 8192: 509 -> 394 us.  No block moves to
-// another stream, so no call ever waits for another stream's work.
+// synchronisation, 8192 x 8192: 509 -> 394 us.  No block moves to another
+// stream, so no call's work waits for another stream's.
 //
 // At most kKeepBytes a device (and kKeepBlocks blocks) are kept; beyond that
-// the stream's own blocks released longest ago make room, or else the newest
-// is freed at once.  ata_release_caches frees all of them, and so does any
-// allocation of the library outside a capture that finds the device's memory
-// exhausted, before it tries again.  An event whose stream is gone is never
-// queried or waited for (the runtime looks at the stream): only a stream of the
-// same handle waits for it, and the release waits for the device.  A block is
-// taken off the list while a call uses it, so threads never share one.  Calls under stream capture (whose memory belongs to the graph)
-// and calls on the per-thread default stream (one handle for many streams)
-// allocate as before.
+// the stream's own blocks released longest ago make room, or else the call
+// allocates without keeping (a block that no longer fits when it is released
+// is freed at once).  A stream that is gone leaves its blocks, and nothing tells
+// it from one that is idle: when a call finds no room and blocks not used for
+// kStale hold half of what may be kept, they are freed after a wait for the
+// device.  Streams in use never come to that wait, however many there are.
+// ata_release_caches frees all of them, and so does any allocation of the
+// library outside a capture that finds the device's memory exhausted, before it
+// tries again.  An event whose stream is gone is never queried or waited for
+// (the runtime looks at the stream): only a stream of the same handle waits for
+// it, and the release waits for the device.  A block is taken off the list while
+// a call uses it, so threads never share one.  Calls under stream capture (whose
+// memory belongs to the graph) and calls on the per-thread default stream (one
+// handle for many streams) allocate as before.
 #include <hip/hip_runtime.h>
 
+#include <chrono>
 #include <cstddef>
 #include <cstdint>
 #include <mutex>
@@ -37,6 +43,9 @@ namespace {
 constexpr size_t kKeepBytes = (size_t)512 << 20;
 constexpr int kKeepBlocks = 64;
 constexpr int kDevices = 64;
+constexpr std::chrono::milliseconds kStale(1000);
+
+typedef std::chrono::steady_clock Clock;
 
 struct Kept {
     void* p;
@@ -44,6 +53,7 @@ struct Kept {
     hipEvent_t ev;
     hipStream_t s;
     uint64_t drop;  // the release that waits for the device to free it (0: none)
+    Clock::time_point at;  // when it was released to the shelf
 };
 
 // Blocks of one device in the order of their release.
@@ -56,6 +66,29 @@ struct Shelf {
         for (--n; i < n; ++i) b[i] = b[i + 1];
         bytes -= k.bytes;
         return k;
+    }
+    // Room for a block of s of `need` bytes, its own blocks making way.
+    bool room(hipStream_t s, size_t need) const {
+        int others = 0;
+        size_t held = 0;
+        for (int i = 0; i < n; ++i)
+            if (b[i].s != s || b[i].drop) {
+                ++others;
+                held += b[i].bytes;
+            }
+        return others < kKeepBlocks && held + need <= kKeepBytes;
+    }
+    // Half of what may be kept, or more, has not been used since `before`, by
+    // streams other than s.
+    bool stale(hipStream_t s, Clock::time_point before) const {
+        int old = 0;
+        size_t held = 0;
+        for (int i = 0; i < n; ++i)
+            if (b[i].s != s && !b[i].drop && b[i].at <= before) {
+                ++old;
+                held += b[i].bytes;
+            }
+        return 2 * old >= kKeepBlocks || 2 * held >= kKeepBytes;
     }
 };
 
@@ -72,16 +105,16 @@ size_t block_size(size_t need) {
     return b < ((size_t)64 << 10) ? (size_t)64 << 10 : b;
 }
 
-// Frees the kept blocks of device d (and their events) after the device's
-// work.  They stay listed until the wait has ended, out of reach of calls; if it
+// Frees the kept blocks of device d (and their events) that were released at
+// `before` or earlier, after the device's work.  They stay listed until the wait has ended, out of reach of calls; if it
 // is refused, as while a stream is captured, they are kept as before.
-void drop_blocks(int d) {
+void drop_blocks(int d, Clock::time_point before = Clock::time_point::max()) {
     uint64_t id = 0;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         Shelf& sh = g_shelf[d];
         for (int i = 0; i < sh.n; ++i)
-            if (!sh.b[i].drop) {
+            if (!sh.b[i].drop && sh.b[i].at <= before) {
                 if (!id) id = ++g_drops;
                 sh.b[i].drop = id;
             }
@@ -103,6 +136,7 @@ void drop_blocks(int d) {
             } else if (done) {
                 old[no++] = sh.take(i);
             } else {
+                sh.b[i].at = Clock::now();
                 sh.b[i++].drop = 0;
             }
         }
@@ -151,6 +185,8 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
         return allocate(&out.p, bytes, s, capture);
     }
     out.dev = dev;
+    bool room, stale = false;
+    Clock::time_point before;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         Shelf& sh = g_shelf[dev];
@@ -165,6 +201,20 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
             out.bytes = k.bytes;
             out.ev = k.ev;
         }
+        room = best >= 0 || sh.room(s, out.bytes);
+        if (!room) {
+            before = Clock::now() - kStale;
+            stale = sh.stale(s, before);
+        }
+    }
+    if (stale) {
+        drop_blocks(dev, before);
+        std::lock_guard<std::mutex> lk(g_mu);
+        room = g_shelf[dev].room(s, out.bytes);
+    }
+    if (!room) {  // it could not be kept: no event
+        out.bytes = bytes;
+        return allocate(&out.p, bytes, s, false);
     }
     if (out.p) {
         e = hipStreamWaitEvent(s, out.ev, 0);
@@ -187,7 +237,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
 
 hipError_t scratch_put(Scratch& sc, hipStream_t s) {
     if (!sc.p) return hipSuccess;
-    const Kept mine{sc.p, sc.bytes, sc.ev, s, 0};
+    const Kept mine{sc.p, sc.bytes, sc.ev, s, 0, Clock::now()};
     const int dev = sc.dev;
     sc = Scratch{};
     if (!mine.ev) return hipFreeAsync(mine.p, s);

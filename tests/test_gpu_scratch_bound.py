@@ -1,0 +1,73 @@
+"""The bound of the kept scratch memory, reached with workspaces of known size
+(A A^t of more than 4000 rows copies A^t), on one stream, on several, and by
+streams that are idle."""
+import ctypes
+import time
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+MB = 1 << 20
+
+
+@pytest.fixture()
+def env():
+    torch = pytest.importorskip("torch")
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1902_02104_amd as P
+    P.load()
+    hip = ctypes.CDLL("libamdhip64.so.7")
+
+    def free():
+        torch.cuda.synchronize()
+        return torch.cuda.mem_get_info()[0] // MB
+
+    P.release_caches()
+    yield torch, P, hip, free
+    P.release_caches()
+    torch.cuda.empty_cache()
+
+
+class _Stream:
+    def __init__(self, torch, hip):
+        self.hip, self.h = hip, ctypes.c_void_p()
+        assert hip.hipStreamCreate(ctypes.byref(self.h)) == 0
+        self.s = torch.cuda.ExternalStream(self.h.value)
+
+    def destroy(self):
+        assert self.hip.hipStreamDestroy(self.h) == 0
+
+
+def test_blocks_of_idle_streams_go_back(env):
+    torch, P, hip, free = env
+    print("case: scratch of idle streams", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    A = torch.randint(-4, 5, (20000, 256), generator=gen, device="cuda").to(torch.float64)
+    il = torch.tril_indices(256, 256, device="cuda")
+    ref = (A.t().contiguous() @ A)[il[0], il[1]]
+    out = torch.empty_like(ref)
+    one = P.workspace_bytes(20000, 256) // MB
+    assert one >= 2
+    torch.cuda.synchronize()
+    P.release_caches()
+    before = free()
+    idle = [_Stream(torch, hip) for _ in range(80)]
+    s = _Stream(torch, hip)
+    for x in idle:
+        P.gram(A, out=out, stream=x.s)
+        torch.cuda.synchronize()
+    assert torch.equal(out, ref)
+    held = before - free()
+    assert held >= min(448, 60 * one)
+    time.sleep(1.2)
+    for _ in range(3):
+        out.zero_()
+        torch.cuda.synchronize()
+        P.gram(A, out=out, stream=s.s)
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+    assert held - (before - free()) >= 350  # what the streams themselves hold stays
+    for x in idle + [s]:
+        x.destroy()

@@ -90,7 +90,9 @@ inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
 """
 
 MAIN = r"""
+#include <chrono>
 #include <cstring>
+#include <thread>
 #include <vector>
 #include "ata_internal.h"
 using namespace atalib::detail;
@@ -104,6 +106,7 @@ static hipError_t call(hipStream_t s, size_t bytes) {
     model::working = true;
     return scratch_put(sc, s);
 }
+static void later() { std::this_thread::sleep_for(std::chrono::milliseconds(1100)); }
 static int reuse() {
     hipStream_t s = model::make();
     for (int i = 0; i < 5; ++i) REQUIRE(call(s, 3 * MB) == hipSuccess);
@@ -181,12 +184,53 @@ static int refused_wait() {
     REQUIRE(call(t, 900 * MB) == hipSuccess);
     return 0;
 }
+// Streams that are gone leave their blocks; a new stream gets room when they are old.
+static int dead_streams(size_t bytes, int streams, bool capture) {
+    for (int i = 0; i < streams; ++i) {
+        hipStream_t s = model::make();
+        REQUIRE(call(s, bytes) == hipSuccess);
+        model::destroy(s);
+    }
+    const size_t held = model::used;
+    hipStream_t t = model::make();
+    const int ev = model::events;
+    for (int i = 0; i < 10; ++i) REQUIRE(call(t, bytes) == hipSuccess);
+    REQUIRE(model::events == ev && model::used == held && model::syncs == 0);  // as if nothing were kept
+    later();
+    hipStream_t c = model::make();
+    c->capturing = capture;
+    REQUIRE(call(t, bytes) == hipSuccess);
+    if (capture) {
+        REQUIRE(model::used == held);
+        c->capturing = false;
+        later();
+        REQUIRE(call(t, bytes) == hipSuccess);
+    }
+    REQUIRE(model::used <= held / 4 && model::syncs == 1);  // the new stream's block
+    const int ma = model::mallocs;
+    for (int i = 0; i < 10; ++i) REQUIRE(call(t, bytes) == hipSuccess);
+    REQUIRE(model::mallocs == ma && model::syncs == 1);
+    return 0;
+}
+// More live streams than blocks: never a device wait, no event for those without a block.
+static int live_streams() {
+    std::vector<hipStream_t> s;
+    for (int i = 0; i < 100; ++i) s.push_back(model::make());
+    for (int r = 0; r < 20; ++r)
+        for (hipStream_t x : s) REQUIRE(call(x, MB) == hipSuccess);
+    REQUIRE(model::syncs == 0 && model::events <= 64 && model::used <= 64 * 9 * MB / 8);
+    return 0;
+}
 int main(int, char** v) {
     if (!strcmp(v[1], "reuse")) return reuse();
     if (!strcmp(v[1], "bound")) return bound();
     if (!strcmp(v[1], "oom")) return oom();
     if (!strcmp(v[1], "oom_capture")) return oom_capture();
     if (!strcmp(v[1], "refused_wait")) return refused_wait();
+    if (!strcmp(v[1], "dead_blocks")) return dead_streams(MB, 64, false);
+    if (!strcmp(v[1], "dead_bytes")) return dead_streams(100 * MB, 5, false);
+    if (!strcmp(v[1], "dead_capture")) return dead_streams(MB, 64, true);
+    if (!strcmp(v[1], "live_streams")) return live_streams();
     return 2;
 }
 """
@@ -204,7 +248,8 @@ def model(tmp_path_factory):
     return exe
 
 
-@pytest.mark.parametrize("case", ["reuse", "bound", "oom", "oom_capture", "refused_wait"])
+@pytest.mark.parametrize("case", ["reuse", "bound", "oom", "oom_capture", "refused_wait", "dead_blocks", "dead_bytes",
+                                  "dead_capture", "live_streams"])
 def test_kept_scratch(model, case):
     r = subprocess.run([model, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
