@@ -40,6 +40,45 @@ class _Stream:
         assert self.hip.hipStreamDestroy(self.h) == 0
 
 
+def test_one_stream_makes_room(env):
+    torch, P, hip, free = env
+    print("case: scratch bound, one stream", flush=True)
+    A = torch.zeros((4500, 15000), device="cuda")
+    C = torch.empty(P.tri(4500), device="cuda")
+    P.gram_rows(A[:, :64], out=C)
+    P.release_caches()
+    before = free()
+    most = 0
+    for k in (3000, 6000, 9000, 12000, 15000):  # copies of 51 to 257 MB, 772 in all
+        P.gram_rows(A[:, :k], out=C)
+        most = max(most, before - free())
+        assert before - free() <= 512 + 64
+    assert most >= 350
+    P.release_caches()
+    assert before - free() <= 64
+
+
+def test_streams_share_the_bound(env):
+    torch, P, hip, free = env
+    print("case: scratch bound, several streams", flush=True)
+    A = torch.zeros((4500, 9000), device="cuda")  # a copy of 154 MB a call
+    outs = [torch.empty(P.tri(4500), device="cuda") for _ in range(8)]
+    P.gram_rows(A[:, :64], out=outs[0])
+    streams = [_Stream(torch, hip) for _ in range(8)]
+    torch.cuda.synchronize()
+    P.release_caches()
+    before = free()
+    for _ in range(2):
+        for s, C in zip(streams, outs):
+            P.gram_rows(A, out=C, stream=s.s)
+    held = before - free()
+    assert 350 <= held <= 512 + 64
+    P.release_caches()
+    assert before - free() <= 64
+    for s in streams:
+        s.destroy()
+
+
 def test_blocks_of_idle_streams_go_back(env):
     torch, P, hip, free = env
     print("case: scratch of idle streams", flush=True)
