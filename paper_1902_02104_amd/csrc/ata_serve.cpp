@@ -524,6 +524,50 @@ void fill_info(const Req* q, ata_request_info* info) {
     info->reserved = 0;
 }
 
+// Plans of the request's slabs under these flags, their workspace and the
+// request's footprint in the pool.
+int plan_request(Req& q, int pf) {
+    const ata_request& r = q.r;
+    size_t wsmax = 0, tables = 0;
+    q.plan_acc.reset();
+    q.plan_tail.reset();
+    if (r.m > 0) {
+        const int64_t rows = q.slab_rows ? q.slab_rows : r.m;
+        std::shared_ptr<PlanDev> hp;
+        // a plan that joins grouped launches keeps the tiles those run
+        int rc = get_plan(rows, r.n, q.cutoff, q.variant, q.depth, pf | kPlanNoFine, false, hp);
+        if (rc == ATA_OK && !(pf & kPlanNoFine) && (q.nslab > 1 || !grouped_plan(hp->plan)))
+            rc = get_plan(rows, r.n, q.cutoff, q.variant, q.depth, pf, false, hp);
+        if (rc != ATA_OK) return rc;
+        q.L = ws_layout(rows, r.n, r.dtype, hp->plan.ws_elems, false, hp->plan.opsum_elems);
+        q.plan = hp;
+        wsmax = q.L.total;
+        tables = align_up(hp->host_blob.size());
+        if (q.nslab > 1) {
+            rc = get_plan(rows, r.n, q.cutoff, q.variant, q.depth, pf | kPlanAccumulate, false, q.plan_acc);
+            if (rc != ATA_OK) return rc;
+            q.L_acc = ws_layout(rows, r.n, r.dtype, q.plan_acc->plan.ws_elems, false, q.plan_acc->plan.opsum_elems);
+            wsmax = std::max(wsmax, q.L_acc.total);
+            tables += align_up(q.plan_acc->host_blob.size());
+            const int64_t tail = r.m - (int64_t)(q.nslab - 1) * rows;
+            if (tail != rows) {
+                rc = get_plan(tail, r.n, q.cutoff, q.variant, q.depth, pf | kPlanAccumulate, false, q.plan_tail);
+                if (rc != ATA_OK) return rc;
+                q.L_tail =
+                    ws_layout(tail, r.n, r.dtype, q.plan_tail->plan.ws_elems, false, q.plan_tail->plan.opsum_elems);
+                wsmax = std::max(wsmax, q.L_tail.total);
+                tables += align_up(q.plan_tail->host_blob.size());
+            }
+        }
+        // every slab's workspace layout fits in the largest one's bytes
+        q.L.total = q.L_acc.total = q.L_tail.total = wsmax;
+    }
+    const size_t eb = elem_bytes(r.dtype);
+    q.footprint = (int64_t)(align_up((size_t)r.m * r.n * eb) + align_up((size_t)(r.n * (r.n + 1) / 2) * eb) +
+                            align_up(wsmax) + tables);
+    return ATA_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -581,48 +625,19 @@ int ata_server_submit(ata_server* srv, const ata_request* req, uint64_t* ticket)
     q->cutoff = req->cutoff ? req->cutoff : default_cutoff(req->m, req->n, req->dtype);
     q->flops = (double)req->m * (double)req->n * (double)req->n;
     // footprint from the host plan (no device work on the caller's thread)
-    std::shared_ptr<PlanDev> hp;
-    size_t wsmax = 0, tables = 0;
     if (req->m > 0) {
         q->slab_rows = slab_rows_for(req->m, req->n);
         const int64_t rows = q->slab_rows ? q->slab_rows : req->m;
         q->nslab = q->slab_rows ? (int)((req->m + rows - 1) / rows) : 1;
         if (q->slab_rows && !req->cutoff) q->cutoff = default_cutoff(rows, req->n, req->dtype);
-        // the library's default depth rule for requests that leave it open;
-        // the dtype class always (it selects the plan's split of short last rounds)
-        const int pf = plan_flags(req->max_depth == -2 ? ATA_OPT_ADAPTIVE : 0, req->dtype);
-        // a plan that joins grouped launches keeps the tiles those run
-        rc = get_plan(rows, req->n, q->cutoff, q->variant, q->depth, pf | kPlanNoFine, false, hp);
-        if (rc == ATA_OK && (q->nslab > 1 || !grouped_plan(hp->plan)))
-            rc = get_plan(rows, req->n, q->cutoff, q->variant, q->depth, pf, false, hp);
-        if (rc != ATA_OK) return rc;
-        q->L = ws_layout(rows, req->n, req->dtype, hp->plan.ws_elems, false, hp->plan.opsum_elems);
-        q->plan = hp;
-        wsmax = q->L.total;
-        tables = align_up(hp->host_blob.size());
-        if (q->nslab > 1) {
-            rc = get_plan(rows, req->n, q->cutoff, q->variant, q->depth, pf | kPlanAccumulate, false, q->plan_acc);
-            if (rc != ATA_OK) return rc;
-            q->L_acc = ws_layout(rows, req->n, req->dtype, q->plan_acc->plan.ws_elems, false,
-                                 q->plan_acc->plan.opsum_elems);
-            wsmax = std::max(wsmax, q->L_acc.total);
-            tables += align_up(q->plan_acc->host_blob.size());
-            const int64_t tail = req->m - (int64_t)(q->nslab - 1) * rows;
-            if (tail != rows) {
-                rc = get_plan(tail, req->n, q->cutoff, q->variant, q->depth, pf | kPlanAccumulate, false, q->plan_tail);
-                if (rc != ATA_OK) return rc;
-                q->L_tail = ws_layout(tail, req->n, req->dtype, q->plan_tail->plan.ws_elems, false,
-                                      q->plan_tail->plan.opsum_elems);
-                wsmax = std::max(wsmax, q->L_tail.total);
-                tables += align_up(q->plan_tail->host_blob.size());
-            }
-        }
-        // every slab's workspace layout fits in the largest one's bytes
-        q->L.total = q->L_acc.total = q->L_tail.total = wsmax;
     }
-    const size_t eb = elem_bytes(req->dtype);
-    q->footprint = (int64_t)(align_up((size_t)req->m * req->n * eb) +
-                             align_up((size_t)(req->n * (req->n + 1) / 2) * eb) + align_up(wsmax) + tables);
+    // the library's default depth rule for requests that leave it open;
+    // the dtype class always (it selects the plan's split of short last rounds)
+    const int pf = plan_flags(req->max_depth == -2 ? ATA_OPT_ADAPTIVE : 0, req->dtype);
+    if ((rc = plan_request(*q, pf))) return rc;
+    // fine tiles split K into parts that can take more workspace than the
+    // 128 x 128 tiles: a request that only these let into the pool runs on them
+    if ((size_t)q->footprint > srv->pool.size && (rc = plan_request(*q, pf | kPlanNoFine))) return rc;
     std::lock_guard<std::mutex> lk(srv->mu);
     ++srv->st.submitted;
     if ((size_t)q->footprint > srv->pool.size) {
