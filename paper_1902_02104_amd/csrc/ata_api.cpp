@@ -178,15 +178,13 @@ void serialize(PlanDev& pd) {
         d.tail_parts = ph.tail_parts;
         d.off_tail = off;
         off = align256(off + ph.tail_items.size() * sizeof(WorkItem));
-        for (int md = 0; md < 2; ++md) {
-            d.n_wide[md] = (int)ph.wide_items[md].size();
-            d.off_wide[md] = off;
-            off = align256(off + ph.wide_items[md].size() * sizeof(WorkItem));
-            d.n_wide_tail[md] = (int)ph.wide_tail[md].size();
-            d.wide_parts[md] = ph.wide_parts[md];
-            d.off_wide_tail[md] = off;
-            off = align256(off + ph.wide_tail[md].size() * sizeof(WorkItem));
-        }
+        d.n_wide = (int)ph.wide_items.size();
+        d.off_wide = off;
+        off = align256(off + ph.wide_items.size() * sizeof(WorkItem));
+        d.n_wide_tail = (int)ph.wide_tail.size();
+        d.wide_parts = ph.wide_parts;
+        d.off_wide_tail = off;
+        off = align256(off + ph.wide_tail.size() * sizeof(WorkItem));
     }
     std::vector<char>& host = pd.host_blob;
     host.assign(off ? off : 256, 0);
@@ -203,12 +201,8 @@ void serialize(PlanDev& pd) {
         std::memcpy(host.data() + d.off_cb, ph.combines.data(), ph.combines.size() * sizeof(DevCombine));
         std::memcpy(host.data() + d.off_ops, ph.opsums.data(), ph.opsums.size() * sizeof(DevOpSum));
         std::memcpy(host.data() + d.off_mix, ph.mix_items.data(), ph.mix_items.size() * sizeof(WorkItem));
-        for (int md = 0; md < 2; ++md) {
-            std::memcpy(host.data() + d.off_wide[md], ph.wide_items[md].data(),
-                        ph.wide_items[md].size() * sizeof(WorkItem));
-            std::memcpy(host.data() + d.off_wide_tail[md], ph.wide_tail[md].data(),
-                        ph.wide_tail[md].size() * sizeof(WorkItem));
-        }
+        std::memcpy(host.data() + d.off_wide, ph.wide_items.data(), ph.wide_items.size() * sizeof(WorkItem));
+        std::memcpy(host.data() + d.off_wide_tail, ph.wide_tail.data(), ph.wide_tail.size() * sizeof(WorkItem));
         std::memcpy(host.data() + d.off_tail, ph.tail_items.data(), ph.tail_items.size() * sizeof(WorkItem));
     }
     for (int mode = 0; mode < 2; ++mode) pd.lp_aligned[mode] = lp_windows_aligned(P, mode == 0 ? 2 : 4);
@@ -400,6 +394,8 @@ int get_plan(int64_t m, int64_t n, int64_t cutoff, int variant, int max_depth, i
     if (flags & kPlanNoSplit) po.split_target = 0;
     if (flags & kPlanAccumulate) po.accumulate = true;
     if (flags & kPlanReducedPrecision) po.lp = true;
+    po.lp_mode = (flags & kPlanBf16Pair) ? 0 : 1;
+    if (flags & kPlanNoFine) po.wide = false;
     if (flags & kPlanF64) po.split_tail = 1;
     else if (!(flags & kPlanReducedPrecision)) po.split_tail = 2;
     else if (flags & kPlanBf16Pair) po.split_tail = 3;
@@ -575,7 +571,7 @@ hipError_t enqueue_product(const PlanDev& pdr, const char* dblob, const WsLayout
                                      (const WorkItem*)(pd->blob + ph.off_tg), ph.n_tg, C_lower, W, s,
                                      lp_align(pdr, lp_mode));
             }
-            if (err == hipSuccess && pdr.lp_dma16[lp_mode] && ph.n_wide[lp_mode] >= kWideMin &&
+            if (err == hipSuccess && pdr.lp_dma16[lp_mode] && ph.n_wide >= kWideMin &&
                 L.ldt * (lp_mode == 0 ? 128 : 64) < ((int64_t)1 << 31)) {
                 // classical tiles on wide workgroup tiles, the last, partial
                 // round of them with its K range split over every CU (parts
@@ -583,10 +579,9 @@ hipError_t enqueue_product(const PlanDev& pdr, const char* dblob, const WsLayout
                 ProfScope ps(ATA_KERNEL_GEMM, s);
                 const LpCopy cp{ws + L.t0, t1, (int)L.ldt, scale};
                 err = launch_lp_tile16(lp_mode, out64, true, cp, tb,
-                                       (const WorkItem*)(pd->blob + ph.off_wide[lp_mode]), ph.n_wide[lp_mode],
-                                       (const WorkItem*)(pd->blob + ph.off_wide_tail[lp_mode]),
-                                       ph.n_wide_tail[lp_mode], ph.wide_parts[lp_mode], W + P.lp_tail_off, C_lower, W,
-                                       s);
+                                       (const WorkItem*)(pd->blob + ph.off_wide), ph.n_wide,
+                                       (const WorkItem*)(pd->blob + ph.off_wide_tail), ph.n_wide_tail, ph.wide_parts,
+                                       W + P.lp_tail_off, C_lower, W, s);
                 if (err == hipSuccess && ph.n_cb) {  // sums of split K parts
                     ProfScope ps2(ATA_KERNEL_COMBINE, s);
                     err = launch_combine(out64, (const DevCombine*)(pd->blob + ph.off_cb), ph.n_cb, ph.cb_elems, W,
@@ -923,14 +918,21 @@ int ata_ex_noalloc(const void* A, int64_t m, int64_t n, int64_t lda, void* C_low
     const int64_t c = cutoff ? cutoff : default_cutoff(m, n, dtype);
     std::shared_ptr<PlanDev> pd;
     // host tables only (no device copy of the plan); no K splitting, whose
-    // partial sums would need workspace
-    rc = get_plan(m, n, c, variant, max_depth, plan_flags(flags, dtype) | kPlanNoSplit, false, pd);
-    if (rc != ATA_OK) return rc;
-    const Plan& P = pd->plan;
-    const WsLayout L = ws_layout(m, n, dtype, P.ws_elems, want_equilibrate(flags, P, dtype), P.opsum_elems, P.lp_ops_rows, P.lp_ops_k);
-    if (L.ldt > INT32_MAX) return ATA_EUNSUPPORTED;
-    const size_t tbytes = (pd->host_blob.size() + 255) / 256 * 256;
-    const size_t need = tbytes + L.total;
+    // partial sums would need workspace; without the tables of wide tiles where
+    // those do not fit
+    WsLayout L;
+    size_t tbytes = 0, need = 0;
+    for (int no : {0, kPlanNoFine}) {
+        if (no && need <= (size_t)ATA_NOALLOC_SCRATCH_BYTES) break;
+        rc = get_plan(m, n, c, variant, max_depth, plan_flags(flags, dtype) | kPlanNoSplit | no, false, pd);
+        if (rc != ATA_OK) return rc;
+        const Plan& P = pd->plan;
+        L = ws_layout(m, n, dtype, P.ws_elems, want_equilibrate(flags, P, dtype), P.opsum_elems, P.lp_ops_rows,
+                      P.lp_ops_k);
+        if (L.ldt > INT32_MAX) return ATA_EUNSUPPORTED;
+        tbytes = (pd->host_blob.size() + 255) / 256 * 256;
+        need = tbytes + L.total;
+    }
     if (scratch_used) *scratch_used = need;
     if (need > (size_t)ATA_NOALLOC_SCRATCH_BYTES) return ATA_EWORKSPACE;
     // the plan's tables go to the start of the array, the workspace after them

@@ -16,13 +16,13 @@ namespace detail {
 // Device copy of one plan's tables.
 struct PhaseDev {
     int n_str = 0, n_tg = 0, n_gemm = 0, n_syrk = 0, n_cb = 0, n_ops = 0, n_mix = 0, str_tmax = 0, tg_tmax = 0;
-    // reduced-precision plans, by mode: wide tiles of the phase's classical
-    // tasks and the K-split tiles of their last round
-    int n_wide[2] = {0, 0}, n_wide_tail[2] = {0, 0}, wide_parts[2] = {0, 0};
+    // reduced-precision plans: wide tiles of the phase's classical tasks and
+    // the K-split tiles of their last round
+    int n_wide = 0, n_wide_tail = 0, wide_parts = 0;
     int n_tail = 0, tail_parts = 0;          // FP64: K-split tiles of the last round of the mix launch
     int64_t cb_elems = 0, ops_rows = 0;
-    size_t off_str = 0, off_tg = 0, off_gemm = 0, off_syrk = 0, off_cb = 0, off_ops = 0, off_mix = 0, off_tail = 0;
-    size_t off_wide[2] = {0, 0}, off_wide_tail[2] = {0, 0};
+    size_t off_str = 0, off_tg = 0, off_gemm = 0, off_syrk = 0, off_cb = 0, off_ops = 0, off_mix = 0, off_tail = 0,
+           off_wide = 0, off_wide_tail = 0;
 };
 
 struct PlanDev {
@@ -129,7 +129,7 @@ constexpr int kPlanF64 = 0x100000;
 // Internal plan flag: bfloat16-pair tiles (one resident workgroup per CU).
 constexpr int kPlanBf16Pair = 0x200000;
 // Internal plan flag: no fine tiles (the serving loop's grouped launches run
-// the SYRK items of a plan).
+// the SYRK items of a plan) and no wide ones: the least tables and workspace.
 constexpr int kPlanNoFine = 0x400000;
 // Equilibration in effect for a call with these option flags and this plan.
 bool want_equilibrate(int flags, const Plan& P, int dtype);

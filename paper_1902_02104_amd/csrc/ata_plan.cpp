@@ -774,51 +774,51 @@ std::vector<WorkItem> wide_tile_items(const Plan& P, const Phase& ph, int mode) 
     return items;
 }
 
-// Reduced-precision plans: the wide tiles of every phase, for both modes.
-// When their count leaves a last round of at most half the resident
-// workgroups, those last tiles (the last positions of the launch) become a
-// launch of their own with the K range of each split into parts, so that the
-// round spreads over every CU; the parts' results go to the workspace and are
-// summed in part order.
+// Reduced-precision plans: the wide tiles of every phase.  When their count
+// leaves a last round of at most half the resident workgroups, those last tiles
+// (the last positions of the launch) become a launch of their own with the K
+// range of each split into parts, so that the round spreads over every CU; the
+// parts' results go to the workspace and are summed in part order.
 void lp_wide_tiles(Plan& P) {
-    int64_t most = 0;  // bytes; one launch at a time uses them
-    for (Phase& ph : P.phases)
-        for (int mode = 0; mode < 2; ++mode) {
-            std::vector<WorkItem>& items = ph.wide_items[mode];
-            items = wide_tile_items(P, ph, mode);
-            // not where wide tiles cover over a fifth more than 128 x 128 ones
-            // (narrow or many short blocks): bfloat16 pairs, 262144 x 300
-            // (two thirds more) 395 us wide against 343; 30000 x 1000 (a
-            // ninth more) equal; 20000 x 2048 (a seventeenth more) 380
-            // against 498 to 579
-            const int64_t narrow = (int64_t)(ph.gemm_items.size() + ph.syrk_items.size());
-            if (5 * (int64_t)items.size() * (kWideRows / kGemmTile) * (wide_cols(mode) / kGemmTile) > 6 * narrow)
-                items.clear();
-            const int64_t nb = (int64_t)items.size(), r = nb % kWideMin;
-            if (nb <= kWideMin || r == 0 || r > kWideMin / 2) continue;
-            // plans without K splitting keep to the small FP32 parts: they
-            // run in a fixed scratch array
-            if (mode == 0 && P.opt.split_target <= 0) continue;
-            int parts = (int)(kWideMin / r);
-            for (int64_t q = nb - r; q < nb; ++q) {
-                const int64_t stages = (task_k(P, P.tasks[items[q].task]) + 127) / 128;
-                parts = (int)std::min<int64_t>(parts, stages / 4);
-            }
-            if (parts < 2) continue;
-            for (int64_t q = nb - r; q < nb; ++q)
-                for (int p = 0; p < parts; ++p) {
-                    WorkItem w = items[q];
-                    w.slot = (int32_t)((q - (nb - r)) * parts + p);
-                    ph.wide_tail[mode].push_back(w);
-                }
-            items.resize(nb - r);
-            ph.wide_parts[mode] = parts;
-            // FP64 partial tiles of bfloat16, FP32 ones of e4m3
-            most = std::max<int64_t>(most, r * parts * kWideRows * wide_cols(mode) * (mode == 0 ? 8 : 4));
+    const int mode = P.opt.lp_mode;
+    int64_t most = 0;  // tiles; one launch at a time uses them
+    for (Phase& ph : P.phases) {
+        std::vector<WorkItem>& items = ph.wide_items;
+        items = wide_tile_items(P, ph, mode);
+        // not where wide tiles cover over a fifth more than 128 x 128 ones
+        // (narrow or many short blocks): bfloat16 pairs, 262144 x 300 (two
+        // thirds more) 395 us wide against 343; 30000 x 1000 (a ninth more)
+        // equal; 20000 x 2048 (a seventeenth more) 380 against 498 to 579
+        const int64_t narrow = (int64_t)(ph.gemm_items.size() + ph.syrk_items.size());
+        if (5 * (int64_t)items.size() * (kWideRows / kGemmTile) * (wide_cols(mode) / kGemmTile) > 6 * narrow)
+            items.clear();
+        // too few for a launch of them (see enqueue_product)
+        if ((int64_t)items.size() < kWideMin) items.clear();
+        const int64_t nb = (int64_t)items.size(), r = nb % kWideMin;
+        if (nb <= kWideMin || r == 0 || r > kWideMin / 2) continue;
+        // plans without K splitting keep to the small FP32 parts: they run in
+        // a fixed scratch array
+        if (mode == 0 && P.opt.split_target <= 0) continue;
+        int parts = (int)(kWideMin / r);
+        for (int64_t q = nb - r; q < nb; ++q) {
+            const int64_t stages = (task_k(P, P.tasks[items[q].task]) + 127) / 128;
+            parts = (int)std::min<int64_t>(parts, stages / 4);
         }
+        if (parts < 2) continue;
+        for (int64_t q = nb - r; q < nb; ++q)
+            for (int p = 0; p < parts; ++p) {
+                WorkItem w = items[q];
+                w.slot = (int32_t)((q - (nb - r)) * parts + p);
+                ph.wide_tail.push_back(w);
+            }
+        items.resize(nb - r);
+        ph.wide_parts = parts;
+        most = std::max<int64_t>(most, r * parts);
+    }
     if (most > 0) {
         P.lp_tail_off = P.ws_elems;
-        P.ws_elems += most / 8;
+        // FP64 partial tiles of bfloat16, FP32 ones of e4m3
+        P.ws_elems += most * kWideRows * wide_cols(mode) / (mode == 0 ? 1 : 2);
     }
 }
 
@@ -1061,7 +1061,7 @@ Plan build_plan(int64_t m, int64_t n, const PlanOptions& opt) {
         }
         P.work_items += (int64_t)(ph.str_items.size() + ph.tg_items.size() + ph.gemm_items.size() + ph.syrk_items.size());
     }
-    if (opt.lp) lp_wide_tiles(P);
+    if (opt.lp && opt.wide) lp_wide_tiles(P);
     if (opt.split_tail && opt.split_target > 0) split_tail_rounds(P);
     for (const Phase& ph : P.phases)
         if (ph.tg_tmax == 2 && (!ph.mix_items.empty() || !ph.tg_items.empty())) {

@@ -156,6 +156,8 @@ struct PlanOptions {
     // (operand-sum form) are converted into rows of a separate copy instead
     // of FP32 buffers (see DevOpSum).
     bool lp = false;
+    int lp_mode = 0;   // 0 bfloat16 pairs, 1 e4m3
+    bool wide = true;  // wide tiles where a phase has enough of them
 };
 
 constexpr int kMaxExpandDepth = 2;
@@ -170,11 +172,11 @@ struct Phase {
     std::vector<WorkItem> mix_items;
     std::vector<DevCombine> combines;
     std::vector<DevOpSum> opsums;  // run before the product tiles
-    // Reduced-precision plans, by mode: the classical tasks on wide tiles, and
-    // the tiles of a short last round split into wide_parts K parts (slot =
-    // tile * parts + part).
-    std::vector<WorkItem> wide_items[2], wide_tail[2];
-    int wide_parts[2] = {0, 0};
+    // Reduced-precision plans: the classical tasks on wide tiles, and the tiles
+    // of a short last round split into wide_parts K parts (slot = tile * parts
+    // + part).
+    std::vector<WorkItem> wide_items, wide_tail;
+    int wide_parts = 0;
     // One-term tile launches: the tiles of a short last round (taken off the
     // end of mix_items, or of the phase's one classical list for FP32) split
     // into tail_parts K parts (slot = tile * parts + part).
