@@ -18,6 +18,7 @@
 #include <cstdint>
 
 #include "ata.h"
+#include "ata_device.h"
 #include "ata_internal.h"
 #include "ata_kernels.h"
 
@@ -32,28 +33,6 @@ constexpr int NP = 4 * NB;   // columns of a panel
 
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef double d2_t __attribute__((ext_vector_type(2)));
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
-
-__device__ __forceinline__ int64_t pidx(int64_t i, int64_t j) { return i * (i + 1) / 2 + j; }
-
-// Value of v in lane src (uniform) for every lane, through scalar registers.
-__device__ __forceinline__ double lane_bcast(double v, int src) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ float lane_bcast(float v, int src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
-}
-
-// Orders the LDS accesses of one wave (they complete in order; this keeps the
-// compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
-
-__device__ __forceinline__ void lds_copy16(rsrc_t r, void* lds, uint32_t voff, uint32_t soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
-}
 
 template <typename T>
 __device__ __forceinline__ T buf_load(rsrc_t r, uint32_t off) {

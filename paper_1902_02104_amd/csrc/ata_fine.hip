@@ -29,6 +29,7 @@
 #include <type_traits>
 
 #include "ata.h"
+#include "ata_device.h"
 #include "ata_internal.h"
 #include "ata_kernels.h"
 
@@ -39,15 +40,8 @@ namespace {
 typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef float f2_t __attribute__((ext_vector_type(2)));
 typedef double d2_t __attribute__((ext_vector_type(2)));
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr uint32_t kOOB = 0x80000000u;  // an offset past every record count used here
 constexpr int KFLUSH = 512;             // FP32 rows between adds into FP64
-
-__device__ __forceinline__ int64_t pidx(int64_t r, int64_t q) { return r * (r + 1) / 2 + q; }
-
-__device__ __forceinline__ void lds_copy16(rsrc_t r, void* lds, uint32_t voff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, 0, 0, 0);
-}
 
 // Row a and column c of linear index b in a lower triangle of tiles.
 __device__ __forceinline__ void tri_decode(int b, int& a, int& c) {
@@ -287,11 +281,6 @@ struct AccRows<float, TB> : Acc<float, TB> {
                 }
     }
 };
-
-template <typename OUT>
-__device__ __forceinline__ void store_c(OUT* p, int beta, double v) {
-    *p = beta ? (OUT)((double)*p + v) : (OUT)v;
-}
 
 // One workgroup: tile `tile` of rows [part * rows, part_end(K, part * rows, rows))
 // (every part has rows).

@@ -38,6 +38,7 @@
 #include <type_traits>
 
 #include "ata.h"
+#include "ata_device.h"
 #include "ata_internal.h"
 #include "ata_kernels.h"
 
@@ -50,22 +51,8 @@ typedef float f16_t __attribute__((ext_vector_type(16)));
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
 typedef int i8_t __attribute__((ext_vector_type(8)));
 typedef unsigned int u4_t __attribute__((ext_vector_type(4)));
-typedef __amdgpu_buffer_rsrc_t rsrc_t;
 constexpr uint32_t kOOB = 0x80000000u;  // an offset past every record count used here
 constexpr int KFLUSH = 512;             // FP32 rows between adds into FP64
-
-__device__ __forceinline__ int64_t pidx(int64_t r, int64_t q) { return r * (r + 1) / 2 + q; }
-
-template <typename OUT>
-__device__ __forceinline__ void store_c(OUT* p, int beta, double v) {
-    *p = beta ? (OUT)((double)*p + v) : (OUT)v;
-}
-
-// One 16-byte-per-lane copy into LDS.  A device function of its own: the host
-// pass does not know the 16-byte form and would drop a kernel that holds it.
-__device__ __forceinline__ void lds_copy16(rsrc_t r, void* lds, uint32_t voff, int soff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (__attribute__((address_space(3))) void*)lds, 16, voff, soff, 0, 0);
-}
 
 // Geometry of a workgroup tile: WM x WN waves of RB x CB result blocks of BS.
 // The 128 x 128 tiles, for launches with too few wide ones: eight waves for

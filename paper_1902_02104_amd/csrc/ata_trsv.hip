@@ -23,6 +23,7 @@
 #include <cstdint>
 
 #include "ata.h"
+#include "ata_device.h"
 #include "ata_internal.h"
 #include "ata_kernels.h"
 
@@ -33,8 +34,6 @@ namespace {
 using detail::ProfScope;
 
 constexpr int NB = 64;  // rows of a block
-
-__device__ __forceinline__ int64_t pidx(int64_t i, int64_t j) { return i * (i + 1) / 2 + j; }
 
 template <typename T>
 struct Bits;
@@ -50,17 +49,6 @@ struct Bits<float> {
     static constexpr U kUnset = 0x7FA5C3F1u;
     static constexpr U kQuiet = 0x7FC00000u;
 };
-
-// Value of v in lane src (uniform) for every lane, through scalar registers.
-__device__ __forceinline__ double lane_bcast(double v, int src) {
-    const uint64_t b = __builtin_bit_cast(uint64_t, v);
-    const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, src);
-    const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), src);
-    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ float lane_bcast(float v, int src) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v), src));
-}
 
 template <typename T>
 __device__ __forceinline__ void publish(T* p, T v) {
@@ -110,10 +98,6 @@ __device__ __forceinline__ void await(const T* p, int64_t stride, T (&v)[RC], bo
 #pragma unroll
     for (int r = 0; r < RC; ++r) v[r] = __builtin_bit_cast(T, b[0][r]);
 }
-
-// Orders the LDS accesses of one wave (they complete in order; this keeps the
-// compiler from moving them).
-__device__ __forceinline__ void wave_lds_fence() { __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront"); }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_trsv_init(T* __restrict__ buf, int64_t count, int* __restrict__ counter) {
