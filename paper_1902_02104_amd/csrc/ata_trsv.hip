@@ -125,7 +125,9 @@ __device__ __forceinline__ T substitute(const T* ld, int lane, T x) {
     for (int b = 0; b < 4; ++b) {
         if (b < 3) cols(16 * (b + 1), d[(b + 1) & 1]);
 #pragma unroll
-        for (int c = 0; c < 16; ++c) x -= d[b & 1][c] * lane_bcast(x, FWD ? 16 * b + c : NB - 1 - (16 * b + c));
+        for (int c = 0; c < 16; ++c)
+            if (16 * b + c < NB - 1)  // no row comes after the last
+                x -= d[b & 1][c] * lane_bcast(x, FWD ? 16 * b + c : NB - 1 - (16 * b + c));
     }
     return x;
 }
@@ -147,12 +149,14 @@ __device__ __forceinline__ T column_steps(const T* __restrict__ L, int64_t d0, i
 
 // Solution of a diagonal block (lane = row; zero past its wd rows).  A value
 // that is not finite shows in its own row, so one vote over the finished rows
-// finds every block that substitute may have got wrong.
+// finds every block that substitute may have got wrong (40 ns a block on the
+// chain, what the step of the last column took).
 template <typename T, bool FWD>
 __device__ __forceinline__ T solve_block(const T* ld, const T* __restrict__ L, int64_t d0, int wd, const T* rcp,
                                          int lane, T x) {
     T v = substitute<T, FWD>(ld, lane, x) * rcp[lane];
-    if (!__all(lane >= wd || __builtin_isfinite(v))) v = column_steps<T, FWD>(L, d0, wd, rcp, lane, x);
+    if (__builtin_expect(__any(lane < wd && !__builtin_isfinite(v)), 0))
+        v = column_steps<T, FWD>(L, d0, wd, rcp, lane, x);
     return lane < wd ? v : T(0);
 }
 
