@@ -282,10 +282,13 @@ struct AccRows<float, TB> : Acc<float, TB> {
     }
 };
 
-// One workgroup: tile `tile` of rows [part * rows, part_end(K, part * rows, rows))
-// (every part has rows).
-// ROWS: A holds the operand columns as rows of K elements (A A^t).
-template <typename T, typename OUT, int TB, bool ROWS>
+// One workgroup: tile `tile` of rows [part * rows, min(K, (part + 1) * rows)).
+// ROWS: A holds the operand columns as rows of K elements (A A^t).  LONG: the
+// sums of rows may pass 2^31.  (An instance of its own: the few scalar
+// instructions that differ move the loop in the instruction cache, and that
+// alone took FP32 A A^t of 1400 x 21319 from 352 to 399 us and FP64 1341 x 2280
+// from 137 to 162.)
+template <typename T, typename OUT, int TB, bool ROWS, bool LONG>
 __global__ void __launch_bounds__(256, 2) k_fine(const T* __restrict__ A, int64_t lda, int K, int n, int tiles,
                                                 int parts, int rows, OUT* __restrict__ C, int beta,
                                                 double* __restrict__ part_out) {
@@ -303,8 +306,14 @@ __global__ void __launch_bounds__(256, 2) k_fine(const T* __restrict__ A, int64_
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const bool diag = ti == tj;
     const int ra = part * rows;
-    const int rb = part_end(K, ra, rows);
-    const int nst = part_stages(rb - ra, KS);
+    int rb, nst;
+    if constexpr (LONG) {
+        rb = part_end(K, ra, rows);
+        nst = part_stages(rb - ra, KS);
+    } else {
+        rb = ra + rows < K ? ra + rows : K;
+        nst = rb > ra ? (rb - ra + KS - 1) / KS : 0;
+    }
     const int64_t row_bytes = lda * (int64_t)sizeof(T);
 
     // This lane's chunk of a copy: row lane / CH of the copy's RPC rows,
@@ -457,8 +466,15 @@ template <typename T, typename OUT, int TB, bool ROWS>
 hipError_t fine_t(const T* A, int64_t lda, int K, int n, int parts, int rows, OUT* C, int beta, double* part,
                   hipStream_t s) {
     const int t = (n + TB - 1) / TB, tiles = t * (t + 1) / 2;
-    hipLaunchKernelGGL((k_fine<T, OUT, TB, ROWS>), dim3(tiles * parts), dim3(256), 0, s, A, lda, K, n, tiles, parts, rows, C,
-                       beta, parts > 1 ? part : (double*)nullptr);
+    double* const po = parts > 1 ? part : nullptr;
+    const dim3 grid(tiles * parts), block(256);
+    // rows of A^t fit 32 bits (their bytes do)
+    if (!ROWS && long_rows(parts, rows))
+        hipLaunchKernelGGL((k_fine<T, OUT, TB, false, true>), grid, block, 0, s, A, lda, K, n, tiles, parts, rows, C, beta,
+                           po);
+    else
+        hipLaunchKernelGGL((k_fine<T, OUT, TB, ROWS, false>), grid, block, 0, s, A, lda, K, n, tiles, parts, rows, C,
+                           beta, po);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || parts <= 1) return e;
     const dim3 g(tiles, TB * TB / 64);

@@ -249,9 +249,12 @@ constexpr int64_t atb_chunks(int64_t m, int64_t n, int64_t nrhs) {
 }
 // Rows of a fine-tile part (k_fine): part p of K rows starts at p * rows and
 // ends at part_end; stages of ks rows.  K goes up to INT32_MAX and parts x rows
-// is K rounded up, so nothing here is formed past K.
-constexpr int part_end(int K, int first, int rows) { return K - first < rows ? K : first + rows; }
-constexpr int part_stages(int rows, int ks) { return rows / ks + (rows % ks != 0); }
+// is K rounded up to stages, so the sums are unsigned where long_rows holds.
+constexpr bool long_rows(int parts, int rows) { return (int64_t)parts * rows > INT32_MAX - 64; }
+constexpr int part_end(int K, int first, int rows) {
+    return (unsigned)first + (unsigned)rows < (unsigned)K ? first + rows : K;
+}
+constexpr int part_stages(int rows, int ks) { return (int)(((unsigned)rows + (unsigned)ks - 1) / (unsigned)ks); }
 constexpr int kStrTile = 64;    // TK_STR quadrant tile (4 quadrants per workgroup)
 // Largest row stride in bytes: kernels address a staged slab of rows with
 // 32-bit offsets.

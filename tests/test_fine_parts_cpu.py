@@ -19,6 +19,8 @@ using namespace atalib;
 static_assert(part_end(INT_MAX, 511 * 4194304, 4194304) == INT_MAX, "");
 static_assert(part_end(INT_MAX, 0, INT_MAX) == INT_MAX, "");
 static_assert(part_stages(INT_MAX, 32) == 67108864, "");
+// (the plain sums of the other calls: ra + rows and rb - ra + KS - 1, KS at most 32)
+static_assert(!long_rows(511, 4194304) && long_rows(512, 4194304) && long_rows(1, INT_MAX - 32), "");
 static_assert(part_end(100, 64, 32) == 96 && part_end(100, 96, 32) == 100 && part_stages(4, 8) == 1, "");
 int main(int argc, char** argv) {
     const long long m = atoll(argv[1]), n = atoll(argv[2]);
