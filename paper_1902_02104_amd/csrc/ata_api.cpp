@@ -396,6 +396,7 @@ int get_plan(int64_t m, int64_t n, int64_t cutoff, int variant, int max_depth, i
     if (flags & kPlanReducedPrecision) po.lp = true;
     po.lp_mode = (flags & kPlanBf16Pair) ? 0 : 1;
     if (flags & kPlanNoFine) po.wide = false;
+    po.by_rows = (flags & kPlanRows) != 0;
     if (flags & kPlanF64) po.split_tail = 1;
     else if (!(flags & kPlanReducedPrecision)) po.split_tail = 2;
     else if (flags & kPlanBf16Pair) po.split_tail = 3;
@@ -974,7 +975,7 @@ int ata_aat(const void* A, int64_t m, int64_t n, int64_t lda, void* C_lower, int
         std::shared_ptr<PlanDev> pd;
         HIP_TRY(hipGetDevice(&dev));
         const int prc = get_plan(n, m, cutoff ? cutoff : default_cutoff(n, m, dtype), variant, max_depth,
-                                 plan_flags(flags, dtype), true, pd);
+                                 plan_flags(flags, dtype) | kPlanRows, true, pd);
         if (prc != ATA_OK) return prc;
         const Plan& P = pd->plan;
         // In one part tiles of C are stored while others are formed: not where

@@ -131,6 +131,8 @@ constexpr int kPlanBf16Pair = 0x200000;
 // Internal plan flag: no fine tiles (the serving loop's grouped launches run
 // the SYRK items of a plan) and no wide ones: the least tables and workspace.
 constexpr int kPlanNoFine = 0x400000;
+// Internal plan flag: the product of A^t for a row-major A (ata_aat).
+constexpr int kPlanRows = 0x800000;
 // Equilibration in effect for a call with these option flags and this plan.
 bool want_equilibrate(int flags, const Plan& P, int dtype);
 int plan_flags(int flags, int dtype);

@@ -895,6 +895,14 @@ void split_tail_rounds(Plan& P) {
 //  * parts cost a second launch (5000) and their partial tiles written and
 //    read back (3 bytes per picosecond for both); up to 1024 rows stay in one
 //    part, at most 16 stages for each wave.
+//  * an FP64 last round of few 128 x 128 tiles starts as slots of the round
+//    before come free: it counts 0.4 of one and four times its share (as a
+//    whole one it sent 7597 x 3061 to 64 x 64 tiles: 1380 us against 1281).
+// FP32 products in one part of either tiles on more than half the CUs: by a fit
+// to 603 timings of 150 to 2000 rows and 2200 to 3968 columns, within 2% for
+// both (the estimate has 64 x 64 tiles too fast near four rounds of them: 672 x
+// 3819 112 us against 97, 842 x 3950 134 against 120).  Not for A A^t, where
+// 128 x 128 tiles wait for a transpose (FP32 3308 x 282 58 us, fine tiles 48).
 bool fine_plan(Plan& P) {
     const PlanOptions& o = P.opt;
     if (!o.fine || P.phases.size() != 1 || P.tasks.size() != 1) return false;
@@ -913,8 +921,11 @@ bool fine_plan(Plan& P) {
     const int64_t want = split ? std::min<int64_t>(64, o.split_target / items) : 1;
     if (want >= 2) p128 = std::max<int64_t>(1, std::min(classical_parts(items, want), k / o.split_min_k));
     const int64_t w128 = items * p128;
-    double best = (double)((k + p128 - 1) / p128) *
-                  (w128 > kCUs ? (double)((w128 + kTileSlots - 1) / kTileSlots) * (f64 ? 236 : 148) : (f64 ? 140 : 82));
+    double rounds = (double)((w128 + kTileSlots - 1) / kTileSlots);
+    if (f64 && !o.by_rows && w128 > kTileSlots)
+        rounds = std::min(rounds, (double)(w128 / kTileSlots) + 0.4 + 4.0 * (double)(w128 % kTileSlots) / kTileSlots);
+    double best =
+        (double)((k + p128 - 1) / p128) * (w128 > kCUs ? rounds * (f64 ? 236 : 148) : (f64 ? 140 : 82));
     if (p128 > 1) best += 5000 + (double)w128 * kGemmTile * kGemmTile * 16 / 3e3;
     int tb = 0;
     int64_t rows = k, parts = 1;
@@ -947,6 +958,11 @@ bool fine_plan(Plan& P) {
     }
     if (!tb) return false;
     const int64_t tl = (n + tb - 1) / tb, tiles = tl * (tl + 1) / 2;
+    if (!f64 && !o.by_rows && tb == 64 && parts == 1 && p128 == 1 && items > kCUs / 2) {
+        const double q = (double)((tiles + kCUs - 1) / kCUs), nn = (double)n * (double)n;
+        if (15.6 * k * q + 1220 * q + 7.6e-4 * nn + 5900 >= (items > kCUs ? 126 : 74.8) * k + 3.5e-4 * nn + 7900)
+            return false;
+    }
     P.fine_tb = tb;
     P.fine_parts = (int32_t)parts;
     P.fine_rows = (int32_t)std::min(rows, k);  // one part: rows is k rounded up to a stage

@@ -152,6 +152,9 @@ struct PlanOptions {
     // may run on 64 x 64 or 32 x 32 tiles (k_fine): 0 never, 1 FP64, 2 FP32.
     // Its K range is split over workgroups only when split_target is set.
     int fine = 0;
+    // The matrix is A^t of a row-major A: fine tiles read it as it is, 128 x 128
+    // tiles after a transpose.
+    bool by_rows = false;
     // Reduced-precision leaves: the operand sums of the Strassen products
     // (operand-sum form) are converted into rows of a separate copy instead
     // of FP32 buffers (see DevOpSum).
