@@ -411,7 +411,8 @@ int ata_server_destroy(ata_server *srv);
  *   C_lower (n x n, packed), in place: on return C_lower holds L, lower
  *   triangular with positive diagonal and L L^t = C.  Panels of 256 columns:
  *   one launch per 64 columns of a panel, then MFMA launches for the trailing
- *   update.  Allocates 64 KB stream-ordered on `stream`.
+ *   update.  Allocates 64 KB stream-ordered on `stream` (n <= 64: one launch, no
+ *   buffer).
  *   info: device int32 or NULL.  The call sets it to 0, and a kernel sets it
  *   to p + 1 for the first column p whose pivot is not positive (LAPACK's
  *   convention); L is then unspecified from column p on.  Read it after the

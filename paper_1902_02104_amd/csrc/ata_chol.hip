@@ -172,6 +172,9 @@ __device__ __forceinline__ void mma_stage(const char* xa, const char* xb, const 
 //     without rows below is stored at once.
 // A pivot that is not positive is reported once through `info` (first failing
 // column + 1, LAPACK's convention); the factorization carries on.
+// SHORT: a matrix of at most 48 columns; the sixteens past its end are left out
+// (an instance of its own, which keeps the chain of larger factors as it is: FP64
+// n = 8 18.0 -> 12.9 us a call, n = 40 19.4 -> 14.4).
 // LDS 79 KB (FP64) and 256 registers: beside one workgroup of the update on the
 // same CU.
 // Measured alone (MI355X): see potrf_t.
@@ -258,7 +261,7 @@ __device__ __noinline__ void factor16_any(T* sx, int b0, int lane, int32_t* info
 // Workgroup barrier for LDS data alone.
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
-template <typename T>
+template <typename T, bool SHORT>
 __global__ __launch_bounds__(256, 2) void k_chol_panel(T* __restrict__ C, int64_t n, int64_t pb, int64_t kb, int w,
                                                     int32_t* __restrict__ info, T* __restrict__ diag,
                                                     const T* __restrict__ prev) {
@@ -409,6 +412,7 @@ __global__ __launch_bounds__(256, 2) void k_chol_panel(T* __restrict__ C, int64_
         lds_barrier();
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
+            if (SHORT && 16 * s >= w) break;
             if (wv == 0) {
                 T d[16];
 #pragma unroll
@@ -432,8 +436,10 @@ __global__ __launch_bounds__(256, 2) void k_chol_panel(T* __restrict__ C, int64_
         lds_barrier();
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
+            if (SHORT && 16 * s >= w) break;
             lds_barrier();
             lds_barrier();
+            if (SHORT) continue;  // no own rows
             // lanes l and l + 32 both hold own row 32 (wv - 2) + (l & 31)
             put(s, lb + NB * LB + 16 * s, LB, NB);
             if (lane < 16) rw[wv - 2][lane] = T(1) / lb[(16 * s + lane) * LB + 16 * s + lane];
@@ -644,7 +650,7 @@ __global__ __launch_bounds__(256, UT == 128 ? 2 : 4) void k_chol_syrk(T* __restr
 // wherever the steps are the longer chain (n = 4000 2362 -> 2282 us, 6000 4119
 // -> 4031, 10000 10620 -> 10470 us), and slower where the updates are (all of
 // n = 10000 on them 11110 us); a line at 3500 or 5500 rows gains less.
-// ws: two 64 x 64 blocks.
+// ws: two 64 x 64 blocks (n <= 64: none).
 // Measured (FP64): a step alone takes 16 us with no panel columns to its left
 // and 6 us more for every 64 (its diagonal block alone took 67 us and the rows
 // below 51 us as launches of their own); the first update at n = 10000 takes
@@ -664,9 +670,14 @@ hipError_t potrf_t(T* C, int64_t n, int32_t* info, T* ws, hipStream_t s, hipStre
             for (int64_t kb = pb; kb < pe; kb += NB) {
                 const int w = (int)(n - kb < NB ? n - kb : NB);
                 const int64_t rest = n - kb - w, step = kb / NB;
-                hipLaunchKernelGGL(k_chol_panel<T>, dim3((unsigned)(rest > 0 ? (rest + NB - 1) / NB : 1)), dim3(256),
-                                   0, s, C, n, pb, kb, w, info, ws + (step & 1) * NB * NB,
-                                   kb > 0 ? ws + ((step - 1) & 1) * NB * NB : (const T*)nullptr);
+                if (n <= 3 * NB / 4)
+                    hipLaunchKernelGGL((k_chol_panel<T, true>), dim3(1), dim3(256), 0, s, C, n, pb, kb, w, info,
+                                       (T*)nullptr, (const T*)nullptr);
+                else
+                    hipLaunchKernelGGL((k_chol_panel<T, false>),
+                                       dim3((unsigned)(rest > 0 ? (rest + NB - 1) / NB : 1)), dim3(256), 0, s, C, n,
+                                       pb, kb, w, info, ws + (step & 1) * NB * NB,
+                                       kb > 0 ? ws + ((step - 1) & 1) * NB * NB : (const T*)nullptr);
                 if ((err = hipGetLastError()) != hipSuccess) return err;
             }
         }
@@ -749,7 +760,8 @@ hipError_t launch_transpose(int elem_bytes, const void* A, int64_t m, int64_t n,
     return hipGetLastError();
 }
 
-size_t potrf_ws_bytes() { return 2 * NB * NB * sizeof(double); }
+// A single block writes C itself.
+size_t potrf_ws_bytes(int64_t n) { return n <= NB ? 0 : 2 * NB * NB * sizeof(double); }
 
 hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, void* ws, hipStream_t s, hipStream_t s2,
                         hipEvent_t e, hipEvent_t f) {

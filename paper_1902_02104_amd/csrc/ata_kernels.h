@@ -146,7 +146,7 @@ hipError_t launch_convert(int mode, const float* x, int64_t count, void* out0, v
 // receives the first failing column + 1 if it is still 0.  ws holds
 // potrf_ws_bytes.  s2: helper stream for the lookahead, with two events e and
 // f; the work on s2 is joined back into s before the call returns.
-size_t potrf_ws_bytes();
+size_t potrf_ws_bytes(int64_t n);
 hipError_t launch_potrf(bool f32, void* C, int64_t n, int32_t* info, void* ws, hipStream_t s, hipStream_t s2,
                         hipEvent_t e, hipEvent_t f);
 // L L^t X = B in place, B row-major n x nrhs with row stride ldb (n, nrhs >= 1);

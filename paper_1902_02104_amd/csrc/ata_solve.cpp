@@ -57,7 +57,7 @@ int potrf_checked(void* C, int64_t n, int dtype, int32_t* info, hipStream_t s) {
         la = nl;
     }
     Scratch ws;
-    SOLVE_TRY(scratch_get(ws, potrf_ws_bytes(), s));
+    if (const size_t bytes = potrf_ws_bytes(n)) SOLVE_TRY(scratch_get(ws, bytes, s));
     hipError_t e = launch_potrf(dtype == ATA_F32, C, n, info, ws.p, s, la.s2, la.e, la.f);
     const hipError_t e2 = scratch_put(ws, s);
     if (e == hipSuccess) e = e2;
