@@ -147,9 +147,9 @@ typedef struct ata_opts {
  * ata_release_caches), unless the stream is being captured or is the
  * per-thread default stream.  It is given back before an allocation of the
  * library fails for want of memory.  Other allocators of the process do not
- * see it: release it before they need the last half gigabyte.  A call that
- * finds the bound taken up by blocks that other streams have not used for a
- * second frees those, after a wait for the device.
+ * see it: release it before they need the last half gigabyte.  (Giving it
+ * back may wait for the device, which ends a capture that another thread is
+ * making.)
  */
 int ata(const void *A, int64_t m, int64_t n, int64_t lda, void *C_lower, int dtype,
         int cutoff, void *stream);

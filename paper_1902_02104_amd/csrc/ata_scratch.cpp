@@ -14,18 +14,23 @@
 // At most kKeepBytes a device (and kKeepBlocks blocks) are kept; beyond that
 // the stream's own blocks released longest ago make room, or else the call
 // allocates without keeping (a block that no longer fits when it is released
-// is freed at once).  A stream that is gone leaves its blocks, and nothing tells
-// it from one that is idle: when a call finds no room and blocks not used for
-// kStale hold half of what may be kept, they are freed after a wait for the
-// device.  Streams in use never come to that wait, however many there are.
-// ata_release_caches frees all of them, and so does any allocation of the
-// library outside a capture that finds the device's memory exhausted, before it
-// tries again.  An event whose stream is gone is never queried or waited for
-// (the runtime looks at the stream): only a stream of the same handle waits for
-// it, and the release waits for the device.  A block is taken off the list while
-// a call uses it, so threads never share one.  Calls under stream capture (whose
-// memory belongs to the graph) and calls on the per-thread default stream (one
-// handle for many streams) allocate as before.
+// is freed at once).  A stream that is gone leaves its blocks, nothing tells it
+// from one that is idle, and an event whose stream is gone is never queried or
+// waited for (the runtime looks at the stream).  So half of what may be kept is
+// held by blocks that a library stream (g_fence) waits for at their release,
+// while their stream is there: when a call finds no room, those of other streams
+// that were not used for kStale are freed on that stream.  (Blocks of the first
+// half do without that wait, 2 to 3 us a block.)  Streams in use never lose blocks to
+// each other.
+//
+// No call waits for the device: that would end any capture in the process with
+// an error.  (Allocations, events and waits of streams for them do not.)  Only
+// ata_release_caches does, which frees every block, and a call outside a capture
+// that finds the device's memory exhausted, after the blocks that can be freed
+// without.  A block is taken off the list while a call uses it, so threads never
+// share one.  Calls under stream capture (whose memory belongs to the graph) and
+// calls on the per-thread default stream (one handle for many streams) allocate
+// as before.
 #include <hip/hip_runtime.h>
 
 #include <chrono>
@@ -53,6 +58,7 @@ struct Kept {
     hipEvent_t ev;
     hipStream_t s;
     uint64_t drop;  // the release that waits for the device to free it (0: none)
+    bool fenced;    // g_fence waits for its work
     Clock::time_point at;  // when it was released to the shelf
 };
 
@@ -78,23 +84,33 @@ struct Shelf {
             }
         return others < kKeepBlocks && held + need <= kKeepBytes;
     }
-    // Half of what may be kept, or more, has not been used since `before`, by
-    // streams other than s.
-    bool stale(hipStream_t s, Clock::time_point before) const {
-        int old = 0;
+    // Whether a block of `need` bytes belongs to the fenced half.
+    bool fence(size_t need) const {
+        int loose = 0;
         size_t held = 0;
         for (int i = 0; i < n; ++i)
-            if (b[i].s != s && !b[i].drop && b[i].at <= before) {
-                ++old;
+            if (!b[i].fenced) {
+                ++loose;
                 held += b[i].bytes;
             }
-        return 2 * old >= kKeepBlocks || 2 * held >= kKeepBytes;
+        return 2 * (loose + 1) > kKeepBlocks || 2 * (held + need) > kKeepBytes;
+    }
+    // Takes the fenced blocks of streams other than s not used since `before`.
+    int retire(hipStream_t s, Clock::time_point before, Kept* out) {
+        int no = 0;
+        for (int i = 0; i < n;)
+            if (b[i].fenced && b[i].s != s && !b[i].drop && b[i].at <= before)
+                out[no++] = take(i);
+            else
+                ++i;
+        return no;
     }
 };
 
 std::mutex g_mu;
 Shelf g_shelf[kDevices];
 uint64_t g_drops = 0;
+hipStream_t g_fence[kDevices];  // made on first use, kept until the process ends
 
 // Block sizes in eighths of a power of two, at least 64 KB: shapes that
 // differ a little share blocks.
@@ -105,16 +121,16 @@ size_t block_size(size_t need) {
     return b < ((size_t)64 << 10) ? (size_t)64 << 10 : b;
 }
 
-// Frees the kept blocks of device d (and their events) that were released at
-// `before` or earlier, after the device's work.  They stay listed until the wait has ended, out of reach of calls; if it
-// is refused, as while a stream is captured, they are kept as before.
-void drop_blocks(int d, Clock::time_point before = Clock::time_point::max()) {
+// Frees the kept blocks of device d (and their events) after the device's work.
+// They stay listed until the wait has ended, out of reach of calls; if it is
+// refused, as while a stream is captured, they are kept as before.
+void drop_blocks(int d) {
     uint64_t id = 0;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         Shelf& sh = g_shelf[d];
         for (int i = 0; i < sh.n; ++i)
-            if (!sh.b[i].drop && sh.b[i].at <= before) {
+            if (!sh.b[i].drop) {
                 if (!id) id = ++g_drops;
                 sh.b[i].drop = id;
             }
@@ -136,7 +152,6 @@ void drop_blocks(int d, Clock::time_point before = Clock::time_point::max()) {
             } else if (done) {
                 old[no++] = sh.take(i);
             } else {
-                sh.b[i].at = Clock::now();
                 sh.b[i++].drop = 0;
             }
         }
@@ -158,14 +173,62 @@ bool capturing(hipStream_t s) {
     return st != hipStreamCaptureStatusNone;
 }
 
+// The fence stream of device d (the current one) waits for event ev.
+hipError_t fence(int d, hipEvent_t ev) {
+    std::lock_guard<std::mutex> lk(g_mu);
+    if (!g_fence[d]) {
+        const hipError_t e = hipStreamCreateWithFlags(&g_fence[d], hipStreamNonBlocking);
+        if (e != hipSuccess) {
+            g_fence[d] = nullptr;
+            return e;
+        }
+    }
+    return hipStreamWaitEvent(g_fence[d], ev, 0);
+}
+
+// Frees blocks taken off the list of device d in the order of stream s (its
+// own blocks) or, fenced ones of other streams, of the fence stream.
+hipError_t free_blocks(int d, const Kept* k, int n, hipStream_t s) {
+    hipError_t e = hipSuccess;
+    for (int i = 0; i < n; ++i) {
+        const bool own = k[i].s == s;
+        const hipError_t e0 = own ? hipStreamWaitEvent(s, k[i].ev, 0) : hipSuccess;
+        const hipError_t e1 = hipFreeAsync(k[i].p, own ? s : g_fence[d]), e2 = hipEventDestroy(k[i].ev);
+        if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1 != hipSuccess ? e1 : e2;
+    }
+    return e;
+}
+
 // Memory from the stream's pool; where there is none left, the kept blocks go
-// back first.  (Not for a capture, which a wait for the device would break.)
-hipError_t allocate(void** p, size_t bytes, hipStream_t s, bool capture) {
+// back first: those that need no wait for the device, then all.  (Not for a
+// capture, which that wait would break.)
+hipError_t allocate(void** p, size_t bytes, hipStream_t s, int d, bool capture) {
     hipError_t e = hipMallocAsync(p, bytes, s);
     if (e == hipErrorOutOfMemory && !capture) {
         (void)hipGetLastError();
-        release_scratch();
-        e = hipMallocAsync(p, bytes, s);
+        if (d >= 0 && d < kDevices) {
+            Kept old[kKeepBlocks];
+            int no = 0;
+            {
+                std::lock_guard<std::mutex> lk(g_mu);
+                Shelf& sh = g_shelf[d];
+                no = sh.retire(s, Clock::time_point::max(), old);
+                for (int i = 0; i < sh.n;)
+                    if (sh.b[i].s == s && !sh.b[i].drop)
+                        old[no++] = sh.take(i);
+                    else
+                        ++i;
+            }
+            if (no) {
+                (void)free_blocks(d, old, no, s);
+                e = hipMallocAsync(p, bytes, s);
+                if (e == hipErrorOutOfMemory) (void)hipGetLastError();
+            }
+        }
+        if (e == hipErrorOutOfMemory) {
+            release_scratch();
+            e = hipMallocAsync(p, bytes, s);
+        }
     }
     if (e != hipSuccess) *p = nullptr;
     return e;
@@ -182,11 +245,12 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
     const bool capture = capturing(s);
     if (out.bytes > kKeepBytes || dev < 0 || dev >= kDevices || capture || s == hipStreamPerThread) {
         out.bytes = bytes;
-        return allocate(&out.p, bytes, s, capture);
+        return allocate(&out.p, bytes, s, dev, capture);
     }
     out.dev = dev;
-    bool room, stale = false;
-    Clock::time_point before;
+    bool room;
+    Kept old[kKeepBlocks];
+    int no = 0;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         Shelf& sh = g_shelf[dev];
@@ -203,18 +267,14 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
         }
         room = best >= 0 || sh.room(s, out.bytes);
         if (!room) {
-            before = Clock::now() - kStale;
-            stale = sh.stale(s, before);
+            no = sh.retire(s, Clock::now() - kStale, old);
+            room = sh.room(s, out.bytes);
         }
     }
-    if (stale) {
-        drop_blocks(dev, before);
-        std::lock_guard<std::mutex> lk(g_mu);
-        room = g_shelf[dev].room(s, out.bytes);
-    }
+    if (no && (e = free_blocks(dev, old, no, s)) != hipSuccess) return e;
     if (!room) {  // it could not be kept: no event
         out.bytes = bytes;
-        return allocate(&out.p, bytes, s, false);
+        return allocate(&out.p, bytes, s, dev, false);
     }
     if (out.p) {
         e = hipStreamWaitEvent(s, out.ev, 0);
@@ -227,7 +287,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
     }
     e = hipEventCreateWithFlags(&out.ev, hipEventDisableTiming | hipEventDisableSystemFence);
     if (e != hipSuccess) return e;
-    e = allocate(&out.p, out.bytes, s, false);
+    e = allocate(&out.p, out.bytes, s, dev, false);
     if (e != hipSuccess) {
         (void)hipEventDestroy(out.ev);
         out = Scratch{};
@@ -237,7 +297,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
 
 hipError_t scratch_put(Scratch& sc, hipStream_t s) {
     if (!sc.p) return hipSuccess;
-    const Kept mine{sc.p, sc.bytes, sc.ev, s, 0, Clock::now()};
+    Kept mine{sc.p, sc.bytes, sc.ev, s, 0, false, Clock::now()};
     const int dev = sc.dev;
     sc = Scratch{};
     if (!mine.ev) return hipFreeAsync(mine.p, s);
@@ -247,9 +307,17 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
         (void)hipFreeAsync(mine.p, s);
         return e;
     }
-    Kept old[kKeepBlocks];
-    int no = 0;
+    {
+        std::lock_guard<std::mutex> lk(g_mu);
+        mine.fenced = g_shelf[dev].fence(mine.bytes);
+    }
     bool kept = true;
+    if (mine.fenced && fence(dev, mine.ev) != hipSuccess) {
+        (void)hipGetLastError();
+        kept = false;
+    }
+    Kept old[kKeepBlocks + 1];
+    int no = 0;
     {
         std::lock_guard<std::mutex> lk(g_mu);
         Shelf& sh = g_shelf[dev];
@@ -265,12 +333,8 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
         }
     }
     if (!kept) old[no++] = mine;
-    for (int i = 0; i < no; ++i) {
-        const hipError_t e0 = hipStreamWaitEvent(s, old[i].ev, 0);
-        const hipError_t e1 = hipFreeAsync(old[i].p, s), e2 = hipEventDestroy(old[i].ev);
-        if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1 != hipSuccess ? e1 : e2;
-    }
-    return e;
+    const hipError_t ef = free_blocks(dev, old, no, s);
+    return e == hipSuccess ? ef : e;
 }
 
 hipError_t device_alloc(void** p, size_t bytes) {

@@ -107,6 +107,6 @@ def test_blocks_of_idle_streams_go_back(env):
         P.gram(A, out=out, stream=s.s)
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
-    assert held - (before - free()) >= 350  # what the streams themselves hold stays
+    assert held - (before - free()) >= 200  # the half that a library stream waits for
     for x in idle + [s]:
         x.destroy()

@@ -2,7 +2,8 @@
 makes: device memory with a limit, streams that are destroyed, events and
 captures.  The model ends the program on what the runtime does not allow: a
 wait for an event whose stream is gone, memory freed at once while the device
-works on it, and a device wait that breaks a capture counts as refused."""
+works on it, memory freed on a stream that does not wait for its last use, and
+counts waits for the device, which a capture refuses."""
 import os
 import subprocess
 
@@ -19,10 +20,11 @@ HIP = r"""
 #include <cstdlib>
 #include <map>
 #include <set>
+enum { hipStreamNonBlocking = 1 };
 enum hipError_t { hipSuccess = 0, hipErrorOutOfMemory = 2, hipErrorInvalidHandle = 400, hipErrorStreamCaptureUnsupported = 900 };
 enum hipStreamCaptureStatus { hipStreamCaptureStatusNone = 0, hipStreamCaptureStatusActive = 1 };
-struct hipStream { bool alive = true, capturing = false; };
-struct hipEvent { hipStream* s = nullptr; int generation = 0; };
+struct hipStream { bool alive = true, capturing = false; std::set<long> waits; };
+struct hipEvent { hipStream* s = nullptr; long use = 0; };
 typedef hipStream* hipStream_t;
 typedef hipEvent* hipEvent_t;
 #define hipStreamPerThread ((hipStream_t)2)
@@ -31,6 +33,8 @@ namespace model {
 inline size_t limit = (size_t)1 << 40, used = 0;
 inline int mallocs = 0, events = 0, syncs = 0, busy_frees = 0;
 inline std::map<void*, size_t> blocks;
+inline std::map<void*, std::pair<hipStream_t, long>> last;  // stream and number of a block's last use
+inline long uses = 0;
 inline std::set<hipStream_t> streams;
 inline bool working = false;
 [[noreturn]] inline void fail(const char* what) { printf("model: %s\n", what); exit(3); }
@@ -66,7 +70,17 @@ inline hipError_t release_block(void* p) {
     model::blocks.erase(it);
     return hipSuccess;
 }
-inline hipError_t hipFreeAsync(void* p, hipStream_t s) { model::check(s); return release_block(p); }
+// Work on the block p in stream s, as a call does between get and put.
+inline void work(void* p, hipStream_t s) { model::last[p] = {s, ++model::uses}; model::working = true; }
+inline hipError_t hipFreeAsync(void* p, hipStream_t s) {
+    model::check(s);
+    const auto u = model::last.find(p);
+    if (u != model::last.end() && u->second.first != s &&
+        (s == hipStreamPerThread || !s || s->waits.lower_bound(u->second.second) == s->waits.end()))
+        model::fail("memory freed on a stream that does not wait for its last use");
+    return release_block(p);
+}
+inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = model::make(); return hipSuccess; }
 inline hipError_t hipFree(void* p) {
     if (model::working) model::fail("memory freed under work that may use it");
     return release_block(p);
@@ -81,10 +95,11 @@ inline hipError_t hipDeviceSynchronize() {
 inline hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { *e = new hipEvent; ++model::events; return hipSuccess; }
 inline hipError_t hipEventCreate(hipEvent_t* e) { return hipEventCreateWithFlags(e, 0); }
 inline hipError_t hipEventDestroy(hipEvent_t e) { delete e; return hipSuccess; }
-inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { model::check(s); e->s = s; return hipSuccess; }
+inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) { model::check(s); e->s = s; e->use = model::uses; return hipSuccess; }
 inline hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
     model::check(s);
     model::check(e->s);
+    if (s && s != hipStreamPerThread && e->s != s) s->waits.insert(e->use);
     return hipSuccess;
 }
 """
@@ -103,7 +118,7 @@ static hipError_t call(hipStream_t s, size_t bytes) {
     const hipError_t e = scratch_get(sc, bytes, s);
     if (e != hipSuccess) return e;
     if (!sc.p) model::fail("no memory and no error");
-    model::working = true;
+    work(sc.p, s);
     return scratch_put(sc, s);
 }
 static void later() { std::this_thread::sleep_for(std::chrono::milliseconds(1100)); }
@@ -171,7 +186,7 @@ static int oom_capture() {
     REQUIRE(model::used >= 400 * MB && model::syncs == 0);
     return 0;
 }
-// While another stream captures, the device cannot be waited for: nothing is freed.
+// While another stream captures, the device cannot be waited for: what needs the wait stays.
 static int refused_wait() {
     hipStream_t s = model::make(), t = model::make(), c = model::make();
     model::limit = 1000 * MB;
@@ -179,13 +194,16 @@ static int refused_wait() {
     c->capturing = true;
     REQUIRE(call(t, 900 * MB) == hipErrorOutOfMemory);
     release_scratch();
-    REQUIRE(model::used >= 400 * MB);
+    REQUIRE(model::used >= 200 * MB);
     c->capturing = false;
     REQUIRE(call(t, 900 * MB) == hipSuccess);
     return 0;
 }
-// Streams that are gone leave their blocks; a new stream gets room when they are old.
+// Streams that are gone leave their blocks; a new stream gets room when they are
+// old, without a wait for the device: up to half of what may be kept stays.
 static int dead_streams(size_t bytes, int streams, bool capture) {
+    hipStream_t c = model::make();
+    c->capturing = capture;
     for (int i = 0; i < streams; ++i) {
         hipStream_t s = model::make();
         REQUIRE(call(s, bytes) == hipSuccess);
@@ -195,21 +213,25 @@ static int dead_streams(size_t bytes, int streams, bool capture) {
     hipStream_t t = model::make();
     const int ev = model::events;
     for (int i = 0; i < 10; ++i) REQUIRE(call(t, bytes) == hipSuccess);
-    REQUIRE(model::events == ev && model::used == held && model::syncs == 0);  // as if nothing were kept
+    REQUIRE(model::events == ev && model::used == held);  // as if nothing were kept
     later();
-    hipStream_t c = model::make();
-    c->capturing = capture;
     REQUIRE(call(t, bytes) == hipSuccess);
-    if (capture) {
-        REQUIRE(model::used == held);
-        c->capturing = false;
-        later();
-        REQUIRE(call(t, bytes) == hipSuccess);
-    }
-    REQUIRE(model::used <= held / 4 && model::syncs == 1);  // the new stream's block
+    REQUIRE(model::used <= held / 2 + bytes + bytes / 8);
     const int ma = model::mallocs;
     for (int i = 0; i < 10; ++i) REQUIRE(call(t, bytes) == hipSuccess);
-    REQUIRE(model::mallocs == ma && model::syncs == 1);
+    REQUIRE(model::mallocs == ma && model::syncs == 0);
+    // for every stream that comes after
+    for (int i = 0; i < 200; ++i) {
+        hipStream_t s = model::make();
+        REQUIRE(call(s, bytes) == hipSuccess);
+        model::destroy(s);
+    }
+    later();
+    hipStream_t u = model::make();
+    REQUIRE(call(u, bytes) == hipSuccess);
+    const int mb = model::mallocs;
+    for (int i = 0; i < 10; ++i) REQUIRE(call(u, bytes) == hipSuccess);
+    REQUIRE(model::mallocs == mb && model::syncs == 0 && model::used <= 512 * MB);
     return 0;
 }
 // More live streams than blocks: never a device wait, no event for those without a block.
