@@ -187,16 +187,26 @@ hipError_t fence(int d, hipEvent_t ev) {
 }
 
 // Frees blocks taken off the list of device d in the order of stream s (its
-// own blocks) or, fenced ones of other streams, of the fence stream.
-hipError_t free_blocks(int d, const Kept* k, int n, hipStream_t s) {
-    hipError_t e = hipSuccess;
+// own blocks) or, fenced ones of other streams, of the fence stream.  Blocks that
+// cannot be freed now go back on the list (the runtime refuses it on a stream
+// that synchronises with the null stream while another such stream is captured).
+void free_blocks(int d, const Kept* k, int n, hipStream_t s) {
     for (int i = 0; i < n; ++i) {
         const bool own = k[i].s == s;
-        const hipError_t e0 = own ? hipStreamWaitEvent(s, k[i].ev, 0) : hipSuccess;
-        const hipError_t e1 = hipFreeAsync(k[i].p, own ? s : g_fence[d]), e2 = hipEventDestroy(k[i].ev);
-        if (e == hipSuccess) e = e0 != hipSuccess ? e0 : e1 != hipSuccess ? e1 : e2;
+        hipError_t e = own ? hipStreamWaitEvent(s, k[i].ev, 0) : hipSuccess;
+        if (e == hipSuccess) e = hipFreeAsync(k[i].p, own ? s : g_fence[d]);
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            std::lock_guard<std::mutex> lk(g_mu);
+            Shelf& sh = g_shelf[d];
+            if (sh.n < kKeepBlocks) {
+                sh.b[sh.n++] = k[i];
+                sh.bytes += k[i].bytes;
+                continue;
+            }
+        }
+        (void)hipEventDestroy(k[i].ev);
     }
-    return e;
 }
 
 // Memory from the stream's pool; where there is none left, the kept blocks go
@@ -220,7 +230,7 @@ hipError_t allocate(void** p, size_t bytes, hipStream_t s, int d, bool capture) 
                         ++i;
             }
             if (no) {
-                (void)free_blocks(d, old, no, s);
+                free_blocks(d, old, no, s);
                 e = hipMallocAsync(p, bytes, s);
                 if (e == hipErrorOutOfMemory) (void)hipGetLastError();
             }
@@ -271,7 +281,7 @@ hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
             room = sh.room(s, out.bytes);
         }
     }
-    if (no && (e = free_blocks(dev, old, no, s)) != hipSuccess) return e;
+    free_blocks(dev, old, no, s);
     if (!room) {  // it could not be kept: no event
         out.bytes = bytes;
         return allocate(&out.p, bytes, s, dev, false);
@@ -333,8 +343,8 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s) {
         }
     }
     if (!kept) old[no++] = mine;
-    const hipError_t ef = free_blocks(dev, old, no, s);
-    return e == hipSuccess ? ef : e;
+    free_blocks(dev, old, no, s);
+    return hipSuccess;
 }
 
 hipError_t device_alloc(void** p, size_t bytes) {

@@ -33,7 +33,7 @@ def env():
 class _Stream:
     def __init__(self, torch, hip):
         self.hip, self.h = hip, ctypes.c_void_p()
-        assert hip.hipStreamCreate(ctypes.byref(self.h)) == 0
+        assert hip.hipStreamCreateWithFlags(ctypes.byref(self.h), 1) == 0  # non-blocking
         self.s = torch.cuda.ExternalStream(self.h.value)
 
     def destroy(self):
@@ -109,4 +109,49 @@ def test_blocks_of_idle_streams_go_back(env):
         assert torch.equal(out, ref)
     assert held - (before - free()) >= 200  # the half that a library stream waits for
     for x in idle + [s]:
+        x.destroy()
+
+
+def test_capture_survives_eager_calls_that_find_no_room(env):
+    """A capture on one stream while an eager call on another takes the place of
+    idle blocks, which must not wait for the device.  (HIP calls by hand: a
+    capture that ends with an error is an error code here.)"""
+    torch, P, hip, free = env
+    print("case: scratch beside a capture", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    A = torch.randint(-4, 5, (20000, 256), generator=gen, device="cuda").to(torch.float64)
+    il = torch.tril_indices(256, 256, device="cuda")
+    ref = (A.t().contiguous() @ A)[il[0], il[1]]
+    C, D = torch.empty_like(ref), torch.zeros_like(ref)
+    idle = [_Stream(torch, hip) for _ in range(80)]
+    other, s = _Stream(torch, hip), _Stream(torch, hip)
+    P.gram(A, out=C)  # the plan is made
+    for x in idle:
+        P.gram(A, out=C, stream=x.s)
+    torch.cuda.synchronize()
+    time.sleep(1.2)
+    before = free()
+    for mode in (0, 1, 2):
+        C.zero_()
+        D.zero_()
+        torch.cuda.synchronize()
+        graph, exe = ctypes.c_void_p(), ctypes.c_void_p()
+        assert hip.hipStreamBeginCapture(s.h, mode) == 0
+        try:
+            P.gram(A, out=C, stream=other.s)
+            P.gram(A, out=D, stream=s.s)
+        finally:
+            ended = hip.hipStreamEndCapture(s.h, ctypes.byref(graph))
+            hip.hipGetLastError()
+        assert ended == 0
+        assert hip.hipGraphInstantiate(ctypes.byref(exe), graph, None, None, ctypes.c_size_t(0)) == 0
+        for _ in range(3):
+            D.zero_()
+            torch.cuda.synchronize()
+            assert hip.hipGraphLaunch(exe, s.h) == 0
+            torch.cuda.synchronize()
+            assert torch.equal(D, ref) and torch.equal(C, ref)
+        assert hip.hipGraphExecDestroy(exe) == 0 and hip.hipGraphDestroy(graph) == 0
+    assert free() - before >= 150  # the idle blocks went back
+    for x in idle + [other, s]:
         x.destroy()

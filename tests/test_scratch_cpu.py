@@ -36,7 +36,7 @@ inline std::map<void*, size_t> blocks;
 inline std::map<void*, std::pair<hipStream_t, long>> last;  // stream and number of a block's last use
 inline long uses = 0;
 inline std::set<hipStream_t> streams;
-inline bool working = false;
+inline bool working = false, refuse = false;
 [[noreturn]] inline void fail(const char* what) { printf("model: %s\n", what); exit(3); }
 inline hipStream_t make() { hipStream_t s = new hipStream; streams.insert(s); return s; }
 inline void destroy(hipStream_t s) { s->alive = false; }  // never reused: its address marks a stale handle
@@ -74,6 +74,7 @@ inline hipError_t release_block(void* p) {
 inline void work(void* p, hipStream_t s) { model::last[p] = {s, ++model::uses}; model::working = true; }
 inline hipError_t hipFreeAsync(void* p, hipStream_t s) {
     model::check(s);
+    if (model::refuse) return hipErrorStreamCaptureUnsupported;
     const auto u = model::last.find(p);
     if (u != model::last.end() && u->second.first != s &&
         (s == hipStreamPerThread || !s || s->waits.lower_bound(u->second.second) == s->waits.end()))
@@ -234,6 +235,33 @@ static int dead_streams(size_t bytes, int streams, bool capture) {
     REQUIRE(model::mallocs == mb && model::syncs == 0 && model::used <= 512 * MB);
     return 0;
 }
+// A block that cannot be freed now is not lost.
+static int refused_free() {
+    for (int i = 0; i < 64; ++i) {
+        hipStream_t s = model::make();
+        REQUIRE(call(s, MB) == hipSuccess);
+        model::destroy(s);
+    }
+    later();
+    hipStream_t t = model::make();
+    Scratch sc;
+    model::refuse = true;
+    REQUIRE(scratch_get(sc, MB, t) == hipSuccess);
+    work(sc.p, t);
+    model::refuse = false;
+    REQUIRE(scratch_put(sc, t) == hipSuccess);
+    release_scratch();
+    REQUIRE(model::used == 0);
+    std::vector<Scratch> two(2);
+    for (Scratch& x : two) REQUIRE(scratch_get(x, 300 * MB, t) == hipSuccess);
+    for (Scratch& x : two) work(x.p, t);
+    model::refuse = true;
+    for (Scratch& x : two) REQUIRE(scratch_put(x, t) == hipSuccess);
+    model::refuse = false;
+    release_scratch();
+    REQUIRE(model::used == 0);
+    return 0;
+}
 // More live streams than blocks: never a device wait, no event for those without a block.
 static int live_streams() {
     std::vector<hipStream_t> s;
@@ -252,6 +280,7 @@ int main(int, char** v) {
     if (!strcmp(v[1], "dead_blocks")) return dead_streams(MB, 64, false);
     if (!strcmp(v[1], "dead_bytes")) return dead_streams(100 * MB, 5, false);
     if (!strcmp(v[1], "dead_capture")) return dead_streams(MB, 64, true);
+    if (!strcmp(v[1], "refused_free")) return refused_free();
     if (!strcmp(v[1], "live_streams")) return live_streams();
     return 2;
 }
@@ -271,7 +300,7 @@ def model(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["reuse", "bound", "oom", "oom_capture", "refused_wait", "dead_blocks", "dead_bytes",
-                                  "dead_capture", "live_streams"])
+                                  "dead_capture", "refused_free", "live_streams"])
 def test_kept_scratch(model, case):
     r = subprocess.run([model, case], capture_output=True, text=True, timeout=60)
     assert r.returncode == 0, r.stdout
