@@ -9,7 +9,7 @@
 // of use, multiplies each with the solved values as soon as they appear, and
 // solves its own diagonal block when the last of them is in.  The chain then
 // costs, per two blocks, one trip of the solved values through memory, two
-// sums over waves and 128 dependent multiply-adds, instead of two launches.
+// sums over waves and 126 dependent multiply-adds, instead of two launches.
 //
 // Solved values pass between workgroups through a buffer that starts filled
 // with a signalling-NaN pattern no arithmetic produces.  Each value is
