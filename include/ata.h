@@ -150,6 +150,10 @@ typedef struct ata_opts {
  * see it: release it before they need the last half gigabyte.  (Giving it
  * back may wait for the device, which ends a capture that another thread is
  * making.)
+ *
+ * Under capture the memory of a call is a memory node of the graph.  A graph
+ * that held several at once failed at its replay: capture one call that
+ * allocates in a graph, or give ata_ex its workspace.
  */
 int ata(const void *A, int64_t m, int64_t n, int64_t lda, void *C_lower, int dtype,
         int cutoff, void *stream);
@@ -449,6 +453,8 @@ int ata_atb(const void *A, int64_t m, int64_t n, int64_t lda, const void *B, int
  *   default; default options), ata_potrf, ata_atb and ata_potrs.  X: row-major
  *   n x nrhs (row stride ldx >= nrhs).  The packed product and the partial
  *   sums are allocated stream-ordered on `stream`.  info as for ata_potrf.
+ *   ATA_EUNSUPPORTED while `stream` is captured (n > 0): see the note on
+ *   capture at ata.
  */
 int ata_normal_solve(const void *A, int64_t m, int64_t n, int64_t lda, const void *B, int64_t nrhs, int64_t ldb,
                      void *X, int64_t ldx, int dtype, int cutoff, int32_t *info, void *stream);
@@ -459,7 +465,8 @@ int ata_normal_solve(const void *A, int64_t m, int64_t n, int64_t lda, const voi
  *   equations: ata_normal_solve into a stream-ordered n x nrhs workspace,
  *   then A X (FP64 sums).  B, out: row-major
  *   m x nrhs (row strides ldb, ldo >= nrhs).  info as for ata_potrf.
- *   n = 0 gives zeros.
+ *   n = 0 gives zeros.  ATA_EUNSUPPORTED while `stream` is captured, as
+ *   ata_normal_solve.
  */
 int ata_project(const void *A, int64_t m, int64_t n, int64_t lda, const void *B, int64_t nrhs, int64_t ldb,
                 void *out, int64_t ldo, int dtype, int cutoff, int32_t *info, void *stream);

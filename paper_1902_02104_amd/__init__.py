@@ -443,7 +443,8 @@ def atb(A, B, out=None, stream=None):
 def normal_solve(A, B, cutoff: int = 0, X=None, info=None, stream=None):
     """Least-squares solution X = (A^t A)^-1 A^t B through the normal
     equations: the packed product, its Cholesky factor, A^t B and the two
-    triangular solves, all on the device.  info as for cholesky().  Returns X."""
+    triangular solves, all on the device.  info as for cholesky().  Not on a
+    stream that is being captured.  Returns X."""
     import torch
     lib = load()
     if A.dim() != 2 or not A.is_cuda:
@@ -472,7 +473,8 @@ def normal_solve(A, B, cutoff: int = 0, X=None, info=None, stream=None):
 def project(A, B, cutoff: int = 0, out=None, info=None, stream=None):
     """P B for the projection P = A (A^t A)^-1 A^t onto the columns of A
     (device tensors; B of length m or m x r): the normal equations on the
-    device, then A X.  info as for cholesky().  Returns out."""
+    device, then A X.  info as for cholesky().  Not on a stream that is being
+    captured.  Returns out."""
     import torch
     lib = load()
     if A.dim() != 2 or not A.is_cuda:

@@ -996,8 +996,18 @@ int ata_aat(const void* A, int64_t m, int64_t n, int64_t lda, void* C_lower, int
         }
     }
     Scratch At;
+    size_t ws_bytes = 0;
+    char* ws = nullptr;
     if (n > 0) {
-        HIP_TRY(scratch_get(At, (size_t)n * (size_t)m * eb, s));
+        size_t bytes = (size_t)n * (size_t)m * eb;
+        if (stream_capturing(s)) {
+            // one memory node in the graph: the product's workspace behind A^t
+            const int wrc = ata_workspace_bytes(n, m, dtype, cutoff, nullptr, &ws_bytes);
+            if (wrc != ATA_OK) return wrc;
+            bytes = (bytes + 255) / 256 * 256 + ws_bytes;
+        }
+        HIP_TRY(scratch_get(At, bytes, s));
+        if (ws_bytes) ws = (char*)At.p + (bytes - ws_bytes);
         const hipError_t e = launch_transpose(eb, A, m, n, lda, At.p, s);
         if (e != hipSuccess) {
             (void)scratch_put(At, s);
@@ -1005,7 +1015,7 @@ int ata_aat(const void* A, int64_t m, int64_t n, int64_t lda, void* C_lower, int
         }
     }
     // A A^t is the product of the n x m matrix A^t with itself: C = (A^t)^t A^t
-    int rc = ata_ex(At.p, n, m, m, C_lower, dtype, cutoff, stream, nullptr, nullptr, 0);
+    int rc = ata_ex(At.p, n, m, m, C_lower, dtype, cutoff, stream, nullptr, ws, ws_bytes);
     const hipError_t e2 = scratch_put(At, s);
     if (rc == ATA_OK && e2 != hipSuccess) rc = hip_fail(e2);
     return rc;

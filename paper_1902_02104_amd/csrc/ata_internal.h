@@ -158,6 +158,8 @@ hipError_t scratch_put(Scratch& sc, hipStream_t s);
 // hipMalloc that gives the kept scratch back where memory has run out.
 hipError_t device_alloc(void** p, size_t bytes);
 void release_scratch();
+// Whether s may be under capture.
+bool stream_capturing(hipStream_t s);
 
 }  // namespace detail
 }  // namespace atalib

@@ -163,16 +163,6 @@ void drop_blocks(int d) {
     (void)hipSetDevice(cur);
 }
 
-// Whether s may be under capture.
-bool capturing(hipStream_t s) {
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
-        (void)hipGetLastError();
-        return true;
-    }
-    return st != hipStreamCaptureStatusNone;
-}
-
 // The fence stream of device d (the current one) waits for event ev.
 hipError_t fence(int d, hipEvent_t ev) {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -246,13 +236,22 @@ hipError_t allocate(void** p, size_t bytes, hipStream_t s, int d, bool capture) 
 
 }  // namespace
 
+bool stream_capturing(hipStream_t s) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return st != hipStreamCaptureStatusNone;
+}
+
 hipError_t scratch_get(Scratch& out, size_t bytes, hipStream_t s) {
     out = Scratch{};
     int dev = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e != hipSuccess) return e;
     out.bytes = block_size(bytes);
-    const bool capture = capturing(s);
+    const bool capture = stream_capturing(s);
     if (out.bytes > kKeepBytes || dev < 0 || dev >= kDevices || capture || s == hipStreamPerThread) {
         out.bytes = bytes;
         return allocate(&out.p, bytes, s, dev, capture);

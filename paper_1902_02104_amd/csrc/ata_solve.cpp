@@ -177,6 +177,9 @@ int ata_normal_solve(const void* A, int64_t m, int64_t n, int64_t lda, const voi
     if (!current_device_ok()) return ATA_EUNSUPPORTED;
     hipStream_t s = (hipStream_t)stream;
     if (n == 0) return potrf_checked(nullptr, 0, dtype, info, s);
+    // Its allocations, one inside another, would be memory nodes of the graph,
+    // and a replay of such a graph ended in a memory violation on the device.
+    if (stream_capturing(s)) return ATA_EUNSUPPORTED;
     const size_t cbytes = (size_t)(n * (n + 1) / 2) * (dtype == ATA_F32 ? 4 : 8);
     Scratch sc;
     SOLVE_TRY(scratch_get(sc, cbytes, s));
@@ -219,6 +222,7 @@ int ata_project(const void* A, int64_t m, int64_t n, int64_t lda, const void* B,
         }
         return rc;
     }
+    if (stream_capturing(s)) return ATA_EUNSUPPORTED;  // as ata_normal_solve
     Scratch sc;
     SOLVE_TRY(scratch_get(sc, ((size_t)n * (size_t)nrhs + kAxPad) * (dtype == ATA_F32 ? 4 : 8), s));
     void* X = sc.p;
