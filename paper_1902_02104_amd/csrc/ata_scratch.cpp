@@ -16,12 +16,13 @@
 // allocates without keeping (a block that no longer fits when it is released
 // is freed at once).  A stream that is gone leaves its blocks, nothing tells it
 // from one that is idle, and an event whose stream is gone is never queried or
-// waited for (the runtime looks at the stream).  So half of what may be kept is
-// held by blocks that a library stream (g_fence) waits for at their release,
+// waited for (the runtime looks at the stream).  So a quarter of what may be kept
+// is held by blocks that a library stream (g_fence) waits for at their release,
 // while their stream is there: when a call finds no room, those of other streams
-// that were not used for kStale are freed on that stream.  (Blocks of the first
-// half do without that wait, 2 to 3 us a block.)  Streams in use never lose blocks to
-// each other.
+// that were not used for kStale are freed on that stream.  (The first three
+// quarters, kLooseBytes and kLooseBlocks, do without that wait, 2 to 3 us a
+// block: bfloat16 pairs 8192 x 8192, a block of 384 MB, 1603 -> 1608 us with it.)
+// Streams in use never lose blocks to each other.
 //
 // No call waits for the device: that would end any capture in the process with
 // an error.  (Allocations, events and waits of streams for them do not.)  Only
@@ -47,6 +48,8 @@ namespace {
 
 constexpr size_t kKeepBytes = (size_t)512 << 20;
 constexpr int kKeepBlocks = 64;
+constexpr size_t kLooseBytes = kKeepBytes / 4 * 3;
+constexpr int kLooseBlocks = kKeepBlocks / 4 * 3;
 constexpr int kDevices = 64;
 constexpr std::chrono::milliseconds kStale(1000);
 
@@ -84,7 +87,7 @@ struct Shelf {
             }
         return others < kKeepBlocks && held + need <= kKeepBytes;
     }
-    // Whether a block of `need` bytes belongs to the fenced half.
+    // Whether a block of `need` bytes belongs to the fenced quarter.
     bool fence(size_t need) const {
         int loose = 0;
         size_t held = 0;
@@ -93,7 +96,7 @@ struct Shelf {
                 ++loose;
                 held += b[i].bytes;
             }
-        return 2 * (loose + 1) > kKeepBlocks || 2 * (held + need) > kKeepBytes;
+        return loose >= kLooseBlocks || held + need > kLooseBytes;
     }
     // Takes the fenced blocks of streams other than s not used since `before`.
     int retire(hipStream_t s, Clock::time_point before, Kept* out) {
